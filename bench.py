@@ -65,7 +65,8 @@ TRAFFIC_COUNTERS = {
     "c2": (3312.91, 20.91, 262144.0 / 131084.54, 1.0, "69ddd8a1d74f33cd"),
 }
 ROLLOUT_SOURCES = ("rollout_step.h", "rollout_kernels.h", "rollout.hip",
-                   "rollout_onelane_1wave.hip", "rollout_multilane.hip", "plan_internal.h",
+                   "rollout_onelane_1wave.hip", "rollout_multilane.hip",
+                   "rollout_multilane_1wave.hip", "plan_internal.h",
                    "select_common.h", "sample.h")
 
 

@@ -112,7 +112,7 @@ __device__ __forceinline__ void est_step(const RolloutArgs &a, float (&st)[7], f
     wz = fmaf(h, wzd, wz);
     delta = clampf_nan(fmaf(h, dd, delta), -a.delta_max, a.delta_max);
     vx = fmaf(h, ax, vx);
-    vx = (vx < a.vx_min) ? a.vx_min : vx;
+    vx = maxn(vx, a.vx_min);
     st[0] = x;
     st[1] = y;
     st[2] = psi;

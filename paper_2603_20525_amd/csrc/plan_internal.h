@@ -238,10 +238,13 @@ struct TickTable {
 
 // chunk = false: candidates start from s0 with zero cost. chunk = true:
 // they continue from a.state / a.cost. Both run the same step code.
-// one_wave (one lane per candidate only): use the kernels built for launches
-// of at most one wave per SIMD (no four-wave register bound; forward Euler of
-// one substep per interval requests each node's terrain a step ahead); the
-// arithmetic, and so every result, is the same either way.
+// one_wave: use the kernels built for launches of at most one wave per SIMD
+// (forward Euler of one substep per interval requests each node's terrain a
+// step ahead; no four-wave register bound); the arithmetic, and so every
+// result, is the same either way.
+inline bool steps_ahead(const RolloutArgs &a, bool one_wave) {
+    return one_wave && a.S == 1 && a.method == 0;
+}
 hipError_t launch_rollout(const RolloutArgs &a, int lanes, int block, bool chunk, hipStream_t s,
                           bool one_wave = false);
 
@@ -283,7 +286,7 @@ hipError_t launch_rollout_est(const RolloutArgs &a, int block, hipStream_t s);
 // is reported and cleared. s1: every slot has one substep per interval.
 hipError_t launch_rollout_slots(const RolloutArgs *slots, const TickTable &t, int *bad,
                                 SelectOut *ring, uint32_t seq, bool s1, int lanes, int block,
-                                hipStream_t s);
+                                hipStream_t s, bool one_wave = false);
 
 // lanes: 1, 2 or 4 lanes per candidate (wheels split as in the forward).
 hipError_t launch_adjoint_backward(const RolloutArgs &a, int C, const float *ckpt,

@@ -56,17 +56,23 @@ __global__ __launch_bounds__(256) void init_state(const RolloutArgs a) {
 }  // namespace
 
 // Public dispatch: one lane here (or, with one_wave, in
-// rollout_onelane_1wave.hip), two and four lanes in rollout_multilane.hip.
+// rollout_onelane_1wave.hip), two and four lanes in rollout_multilane.hip
+// (or, with one_wave and one Euler step per interval, in
+// rollout_multilane_1wave.hip).
 hipError_t launch_rollout(const RolloutArgs &a, int lanes, int block, bool chunk,
                           hipStream_t s, bool one_wave) {
-    if (lanes != 1) return launch_rollout_multi(a, lanes, block, chunk, s);
+    if (lanes != 1)
+        return steps_ahead(a, one_wave) ? launch_rollout_multi_1wave(a, lanes, block, chunk, s)
+                                        : launch_rollout_multi(a, lanes, block, chunk, s);
     return one_wave ? launch_rollout_1wave(a, block, chunk, s)
                     : launch_rollout_lanes<1>(a, block, chunk, s);
 }
 
 hipError_t launch_rollout_sampled(const RolloutArgs &a, int lanes, int block, hipStream_t s,
                                   bool one_wave) {
-    if (lanes != 1) return launch_sampled_multi(a, lanes, block, s);
+    if (lanes != 1)
+        return steps_ahead(a, one_wave) ? launch_sampled_multi_1wave(a, lanes, block, s)
+                                        : launch_sampled_multi(a, lanes, block, s);
     return one_wave ? launch_sampled_1wave(a, block, s) : launch_sampled_lanes<1>(a, block, s);
 }
 
@@ -76,7 +82,9 @@ hipError_t launch_rollout_ckpt(const RolloutArgs &a, int lanes, int block, hipSt
 
 hipError_t launch_rollout_argmin(const RolloutArgs &a, int lanes, int block, bool sampled,
                                  hipStream_t s, bool one_wave) {
-    if (lanes != 1) return launch_argmin_multi(a, lanes, block, sampled, s);
+    if (lanes != 1)
+        return steps_ahead(a, one_wave) ? launch_argmin_multi_1wave(a, lanes, block, sampled, s)
+                                        : launch_argmin_multi(a, lanes, block, sampled, s);
     return one_wave ? launch_argmin_1wave(a, block, sampled, s)
                     : launch_argmin_lanes<1>(a, block, sampled, s);
 }
@@ -109,10 +117,11 @@ hipError_t launch_rollout_balanced(const RolloutArgs &a, int split, bool sampled
 
 hipError_t launch_rollout_slots(const RolloutArgs *slots, const TickTable &t, int *bad,
                                 SelectOut *ring, uint32_t seq, bool s1, int lanes, int block,
-                                hipStream_t s) {
+                                hipStream_t s, bool one_wave) {
     if (t.count < 1) return hipSuccess;
-    return lanes == 1 ? launch_slots_lanes<1>(slots, t, bad, ring, seq, s1, block, s)
-                      : launch_slots_multi(slots, t, bad, ring, seq, s1, lanes, block, s);
+    if (lanes == 1) return launch_slots_lanes<1>(slots, t, bad, ring, seq, s1, block, s);
+    return one_wave && s1 ? launch_slots_multi_1wave(slots, t, bad, ring, seq, lanes, block, s)
+                          : launch_slots_multi(slots, t, bad, ring, seq, s1, lanes, block, s);
 }
 
 hipError_t launch_sample_controls(const SampleArgs &sa, int K, int N, float *controls,

@@ -1,9 +1,10 @@
 // Rollout kernel templates (SRB model, stage cost, ESM constraint) and, per
-// lane count, their launch dispatch. Three translation units instantiate
-// them: rollout.hip (one lane per candidate), rollout_onelane_1wave.hip (one
-// lane per candidate for launches of at most one wave per SIMD) and
-// rollout_multilane.hip (two and four lanes per candidate). The arithmetic is
-// the same in all, so results are identical for every launch shape.
+// lane count, their launch dispatch. Four translation units instantiate
+// them: rollout.hip (one lane per candidate) and rollout_multilane.hip (two
+// and four lanes per candidate), and rollout_onelane_1wave.hip and
+// rollout_multilane_1wave.hip for launches of at most one wave per SIMD. The
+// arithmetic is the same in all, so results are identical for every launch
+// shape.
 #pragma once
 
 #include "plan_internal.h"
@@ -13,15 +14,13 @@
 namespace plan {
 namespace {
 
-// The kernels built with PLAN_REQUEST_AHEAD (rollout_onelane_1wave.hip: one
-// lane, launches of at most one wave per SIMD) have registers to spare: their
-// Euler kernels with one substep per interval request each node's terrain a
-// whole step ahead (euler_step_ahead), which holds two nodes' cell
-// coefficients in registers at once (190-260 VGPRs). The one-lane kernels
-// for three or four waves per SIMD (the paper's solver shape) need the
-// registers for occupancy; the two- and four-lane kernels measured no gain
-// (a wave there gathers one or two wheels' cells and waits mostly on its
-// own dependency chain).
+// The kernels built with PLAN_REQUEST_AHEAD (rollout_onelane_1wave.hip and
+// rollout_multilane_1wave.hip: launches of at most one wave per SIMD) have
+// registers to spare: their Euler kernels with one substep per interval
+// request each node's terrain a whole step ahead (euler_step_ahead), which
+// holds two nodes' cell coefficients in registers at once. The kernels for
+// more waves per SIMD need the registers for occupancy and hide the gathers
+// behind each other's arithmetic.
 #ifdef PLAN_REQUEST_AHEAD
 constexpr bool REQUEST_AHEAD = true;
 #else
@@ -40,6 +39,8 @@ template <int LANES, bool CHUNK, bool SAMPLED = false, bool RK4 = false, bool CK
 __device__ __forceinline__ float simulate(const RolloutArgs &a, int k, int sub, bool store,
                                           const float *up) {
     constexpr int WPL = 4 / LANES;  // wheels per lane
+    constexpr bool AHEAD = REQUEST_AHEAD && !RK4 && !CKPT && S1;
+    constexpr bool TRIPS = AHEAD && LANES > 1;  // the loop of four-interval trips below
     const size_t K = (size_t)a.K;
 
     float st0[13];
@@ -64,7 +65,7 @@ __device__ __forceinline__ float simulate(const RolloutArgs &a, int k, int sub, 
     float nu0 = 0.0f, nu1 = 0.0f;
     // the pair requested during interval n: interval min(n + 1, n1 - 1)
     const float *unext = up + 2 * (size_t)max(min(a.n0 + 1, a.n1 - 1), 0) * K;
-    if constexpr (!SAMPLED) {
+    if constexpr (!SAMPLED && !TRIPS) {
         if (a.n0 < a.n1) {
             nu0 = up[(2 * (size_t)a.n0) * K];
             nu1 = up[(2 * (size_t)a.n0 + 1) * K];
@@ -72,6 +73,32 @@ __device__ __forceinline__ float simulate(const RolloutArgs &a, int k, int sub, 
     }
     PhiloxBlock blk{};
     int blk_n = -1;
+
+    // SAMPLED at several lanes per candidate: a generator block and its four
+    // draws cost more than a third of a step, so each lane of the group makes
+    // a different block, and an interval's pair comes from the lane that has it
+    // (drawn from intervals base .. base + 4 LANES - 1, lane i's the four from
+    // base + 4 i), restricted to the admissible set there. Gaussian draws,
+    // 12 000 x 60 at two lanes with a costmap: 74.9 -> 49.8 us (with the trips
+    // below)
+    float du0[4], du1[4];
+    auto draw_shared = [&](int base) {
+        const PhiloxBlock b = sample_block(a.smp, k, (base >> 2) + sub);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            draw_controls(a.smp, block_word(b, j), k, min(base + 4 * sub + j, a.N - 1), du0[j],
+                          du1[j]);
+            du0[j] = clampf_nan(du0[j], -a.drate_max, a.drate_max);
+            du1[j] = a.accel_max * clampf_nan(du1[j], -1.0f, 1.0f);
+        }
+    };
+    // byte index of lane ((n / 4) mod LANES) of this lane's group, for ds_bpermute
+    auto owner = [&](int n) {
+        return (((int)(threadIdx.x & 63) & ~(LANES - 1)) + ((n >> 2) & (LANES - 1))) << 2;
+    };
+    auto from_lane = [](int byte, float v) {
+        return __int_as_float(__builtin_amdgcn_ds_bpermute(byte, __float_as_int(v)));
+    };
 
     Arm arms[WPL];
 #pragma unroll
@@ -96,8 +123,122 @@ __device__ __forceinline__ float simulate(const RolloutArgs &a, int k, int sub, 
     // the other, which would wait for the loads in flight. A candidate at its
     // goal skips the step and its requests; it stays frozen, so it never uses
     // a set again.
-    constexpr bool AHEAD = REQUEST_AHEAD && !RK4 && !CKPT && S1;
-    if constexpr (AHEAD) {
+    if constexpr (TRIPS) {
+        // Two and four lanes per candidate: the same two sets, in trips of four
+        // intervals whose controls are requested a whole trip ahead (one pair
+        // of loads brings LANES intervals, interval n + q in lane q % LANES of
+        // the group), so that neither the cells nor the controls of a launch
+        // whose inputs are not in the caches hold a step up. Every lane takes
+        // every step, a candidate past its goal too, so that a trip is one
+        // block in which the number of loads in flight is known (a step that
+        // some path skips makes the compiler wait for a node's requests before
+        // it issues the next one's); the state and cost with which a candidate
+        // first stands at its goal are kept aside, in a branch that a wave
+        // takes once or so per candidate, and put back at the end.
+        // The branch is marked unlikely: a taken branch costs a lone wave the
+        // fetch behind it (2 to 4 us in 100 steps).
+        // Measured against the plain loop, each on inputs that change from
+        // call to call: 10 007 candidates x 73 steps 58.5 -> 45.5 us, with the
+        // softmin, costmap and final states 66.7 -> 55.5 us; 16 000 x 90 with
+        // a costmap 69.4 -> 55.6 us; 25 000 x 100 at two lanes 81.0 -> 72.9
+        // us; 4 096 x 100, whose cells stay in the L2, 58.0 -> 57.2 us.
+        bool done = false;
+        float kept[14];
+#pragma unroll
+        for (int q = 0; q < 13; ++q) kept[q] = st[q];
+        kept[13] = J;
+        auto interval = [&](float dd, float ax, const NodeRequest<LANES, CM> &cur,
+                            NodeRequest<LANES, CM> &nxt) {
+            // goal test at the node, written as in the other loops so that a
+            // NaN position (never at the goal) keeps stepping there as here
+            const float gdx = st[0] - a.goal_x, gdy = st[1] - a.goal_y;
+            const bool arrives = fmaf(gdx, gdx, gdy * gdy) <= a.goal_r2 && !done;
+            if (__builtin_expect(__any(arrives), 0)) {
+#pragma unroll
+                for (int q = 0; q < 13; ++q) kept[q] = arrives ? st[q] : kept[q];
+                kept[13] = arrives ? J : kept[13];
+                done = done || arrives;
+            }
+            euler_step_ahead<LANES, CM>(a, arms, st, J, dd, ax, cur, nxt);
+        };
+        constexpr int PER = 4 / LANES;  // pairs of a trip that a lane holds
+        float cu0[PER], cu1[PER], nu0[PER], nu1[PER];
+        auto request_controls = [&](int n, float (&u0)[PER], float (&u1)[PER]) {
+#pragma unroll
+            for (int q = 0; q < PER; ++q) {
+                const float *p = up + 2 * (size_t)min(n + q * LANES + sub, a.n1 - 1) * K;
+                u0[q] = p[0];
+                u1[q] = p[K];
+            }
+        };
+        // the controls before the cells, here as in the loop, so that waiting
+        // for them never waits for the cells behind them
+        int n = a.n0;
+        if constexpr (!SAMPLED) {
+            if (n < a.n1) request_controls(n, cu0, cu1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        NodeRequest<LANES, CM> P, Q;
+        request_node<LANES, CM>(a, arms, st[0], st[1], st[2], st[3], st[4], st[5], P);
+        for (; n + 3 < a.n1; n += 4) {
+            float u0[4], u1[4];
+            if constexpr (SAMPLED) {
+                if ((n & (4 * LANES - 1)) == 0) draw_shared(n);
+                const int o = owner(n);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    u0[q] = from_lane(o, du0[q]);
+                    u1[q] = from_lane(o, du1[q]);
+                }
+            } else {
+                request_controls(n + 4, nu0, nu1);
+                float cdd[PER], cax[PER];
+#pragma unroll
+                for (int q = 0; q < PER; ++q) {
+                    cdd[q] = clampf_nan(cu0[q], -a.drate_max, a.drate_max);
+                    cax[q] = a.accel_max * clampf_nan(cu1[q], -1.0f, 1.0f);
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    u0[q] = group_lane<LANES>(cdd[q / LANES], q % LANES);
+                    u1[q] = group_lane<LANES>(cax[q / LANES], q % LANES);
+                }
+            }
+            interval(u0[0], u1[0], P, Q);
+            interval(u0[1], u1[1], Q, P);
+            interval(u0[2], u1[2], P, Q);
+            interval(u0[3], u1[3], Q, P);
+            if constexpr (!SAMPLED) {
+#pragma unroll
+                for (int q = 0; q < PER; ++q) {
+                    cu0[q] = nu0[q];
+                    cu1[q] = nu1[q];
+                }
+            }
+            n = __all(done) ? a.n1 : n;  // nothing left to step
+        }
+        // the last one to three intervals
+        for (; n < a.n1; ++n) {
+            float u0, u1;
+            if constexpr (SAMPLED) {
+                if ((n & (4 * LANES - 1)) == 0) draw_shared(n);
+                const int o = owner(n), j = n & 3;
+                u0 = from_lane(o, j == 0 ? du0[0] : j == 1 ? du0[1] : du0[2]);
+                u1 = from_lane(o, j == 0 ? du1[0] : j == 1 ? du1[1] : du1[2]);
+            } else {
+                u0 = up[2 * (size_t)n * K];
+                u1 = up[(2 * (size_t)n + 1) * K];
+                u0 = clampf_nan(u0, -a.drate_max, a.drate_max);
+                u1 = a.accel_max * clampf_nan(u1, -1.0f, 1.0f);
+            }
+            interval(u0, u1, P, Q);
+            P = Q;
+        }
+        // nothing is taken from a step past the goal
+#pragma unroll
+        for (int q = 0; q < 13; ++q) st[q] = done ? kept[q] : st[q];
+        J = done ? kept[13] : J;
+    } else if constexpr (AHEAD) {
         auto interval = [&](int n, const NodeRequest<LANES, CM> &cur,
                             NodeRequest<LANES, CM> &nxt) {
             float u0, u1;
@@ -144,7 +285,12 @@ __device__ __forceinline__ float simulate(const RolloutArgs &a, int k, int sub, 
         // zero-order hold: control n for the whole interval, restricted to the
         // admissible set (|delta_dot| <= limit, throttle in [-1, 1])
         float u0, u1;
-        if constexpr (SAMPLED) {
+        if constexpr (SAMPLED && LANES > 1) {
+            if ((n & (4 * LANES - 1)) == 0) draw_shared(n);  // n0 = 0
+            const int o = owner(n), j = n & 3;
+            u0 = from_lane(o, j == 0 ? du0[0] : j == 1 ? du0[1] : j == 2 ? du0[2] : du0[3]);
+            u1 = from_lane(o, j == 0 ? du1[0] : j == 1 ? du1[1] : j == 2 ? du1[2] : du1[3]);
+        } else if constexpr (SAMPLED) {
             if ((n >> 2) != blk_n) {
                 blk_n = n >> 2;
                 blk = sample_block(a.smp, k, blk_n);
@@ -160,8 +306,9 @@ __device__ __forceinline__ float simulate(const RolloutArgs &a, int k, int sub, 
                 }
             }
         }
-        const float dd = clampf_nan(u0, -a.drate_max, a.drate_max);
-        const float ax = a.accel_max * clampf_nan(u1, -1.0f, 1.0f);
+        constexpr bool DRAWN = SAMPLED && LANES > 1;
+        const float dd = DRAWN ? u0 : clampf_nan(u0, -a.drate_max, a.drate_max);
+        const float ax = DRAWN ? u1 : a.accel_max * clampf_nan(u1, -1.0f, 1.0f);
 
         // S1: one Euler substep per interval, no substep loop
         const int S = S1 ? 1 : a.S;
@@ -522,6 +669,17 @@ __forceinline__ hipError_t launch_slots_lanes(const RolloutArgs *slots, const Ti
 hipError_t launch_rollout_1wave(const RolloutArgs &a, int block, bool chunk, hipStream_t s);
 hipError_t launch_sampled_1wave(const RolloutArgs &a, int block, hipStream_t s);
 hipError_t launch_argmin_1wave(const RolloutArgs &a, int block, bool sampled, hipStream_t s);
+
+// Two- and four-lane dispatch of the launches of at most one wave per SIMD
+// whose intervals are one Euler step, defined in rollout_multilane_1wave.hip.
+hipError_t launch_rollout_multi_1wave(const RolloutArgs &a, int lanes, int block, bool chunk,
+                                      hipStream_t s);
+hipError_t launch_sampled_multi_1wave(const RolloutArgs &a, int lanes, int block, hipStream_t s);
+hipError_t launch_argmin_multi_1wave(const RolloutArgs &a, int lanes, int block, bool sampled,
+                                     hipStream_t s);
+hipError_t launch_slots_multi_1wave(const RolloutArgs *slots, const TickTable &t, int *bad,
+                                    SelectOut *ring, uint32_t seq, int lanes, int block,
+                                    hipStream_t s);
 
 // Two- and four-lane dispatch, defined in rollout_multilane.hip.
 hipError_t launch_rollout_multi(const RolloutArgs &a, int lanes, int block, bool chunk,

@@ -346,7 +346,8 @@ static plan_status_t launch_step(plan_server *s) {
     for (int j = 0; j < t.count; ++j)
         s1 = s1 && s->reqs[s->slots[t.e[j].slot].req].r.integ.substeps == 1;
     SHIP(s, plan::launch_rollout_slots(s->slot_args, t, s->bad, s->ring_host[st.ring], st.seq,
-                                       s1, lanes, block, s->stream));
+                                       s1, lanes, block, s->stream,
+                                       (total_K * lanes + 63) / 64 <= s->simds));
     // per-candidate costs of the requests that asked for them, copied before
     // any later launch can reuse the slot
     for (const auto &fr : st.finished) {

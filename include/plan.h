@@ -237,7 +237,10 @@ plan_status_t plan_rollout_chunk(plan_ctx *ctx, float *state_dev, float *cost_de
  * Non-smooth points take the derivative of the branch the forward pass took.
  * The backward kernel splits each candidate's wheels over 1, 2 or 4 lanes
  * (the automatic choice of plan_rollout, or the lanes set by
- * plan_set_launch); the result is bit-identical for every choice.
+ * plan_set_launch); the result is bit-identical for every choice. Up to 24
+ * candidates per compute unit another backward kernel linearises the steps in
+ * parallel; its gradients differ from the first one's by rounding only, and do
+ * not depend on the lanes or on checkpoint_every either.
  * The forward pass is one launch that stores the checkpoints; the backward
  * pass is a second. The library grows an internal workspace of
  * 4*(13 K (ceil(N/C) + 1) + 14 K C S) bytes when a call needs more than the

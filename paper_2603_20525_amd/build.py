@@ -10,7 +10,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libplan.so")
 SOURCES = ["rollout.hip", "rollout_onelane_1wave.hip", "rollout_multilane.hip",
            "rollout_multilane_1wave.hip", "est.hip", "select.hip", "plan_api.hip", "serve.hip",
-           "adjoint.hip", "terrain_prep.hip", "order.hip"]
+           "adjoint.hip", "adjoint_linear.hip", "terrain_prep.hip", "order.hip"]
 
 # Per-source flags (none at present). Every unit uses the default instruction
 # scheduler: the max-ILP scheduler, once 3-4 % faster for the kernels of one

@@ -911,13 +911,35 @@ static plan_status_t grad_check(plan_ctx *c, const char *fn, const float *state0
     return PLAN_OK;
 }
 
+// Checkpoint interval of the parallel backward pass in the workspace that
+// interval C sizes: that pass keeps recomputed states in LDS, so the part meant
+// for them holds checkpoints too. It wants short segments (they are recomputed
+// in parallel), but not under four steps, where the forward pass's stores cost
+// more than the recomputation. The gradient does not depend on it.
+static int linear_interval(int N, int C, int S) {
+    const long long room = 13ll * ((N + C - 1) / C + 1) + 14ll * C * S;
+    long long c = S >= 4 ? 1 : (4 + S - 1) / S;
+    while (c < N && 13 * ((N + c - 1) / c + 1) > room) ++c;
+    return (int)(c < N ? c : N);
+}
+
 // Forward pass with checkpoints, then the backward pass, on workspace ws
 // (at least grad_check's *need floats; every float of it that is read is
 // first written by the same call).
 static plan_status_t grad_launch(plan_ctx *c, const float *state0, const float *controls_dev,
                                  int K, int N, const float *weight_dev, int checkpoint_every,
                                  float *cost_dev, float *grad_dev, float *ws) {
-    const int C = checkpoint_every < N ? checkpoint_every : N;
+    int C = checkpoint_every < N ? checkpoint_every : N;
+    // Up to 24 candidates per compute unit (six rounds of workgroups of four)
+    // the backward pass whose steps are linearised in parallel is faster: N =
+    // 100, C = 10, with the forward pass, against the serial one: K = 16 87
+    // against 257 us, 1 024 105 against 267, 4 096 233 against 288, 6 000 291
+    // against 296; 8 192 294 against 292, 16 384 491 against 309 (that one's
+    // waves have SIMDs to themselves up to there).
+    const int fine = linear_interval(N, C, c->integ.substeps);
+    const bool linear = K <= 6 * c->simds &&
+                        (long long)fine * c->integ.substeps <= plan::ADJOINT_LINEAR_STEPS;
+    if (linear) C = fine;
     const int nseg = (N + C - 1) / C;
     float *ckpt = ws;
     float *seg = ckpt + (size_t)(nseg + 1) * 13 * (size_t)K;
@@ -944,8 +966,11 @@ static plan_status_t grad_launch(plan_ctx *c, const float *state0, const float *
     HIP_TRY(c, plan::launch_rollout_ckpt(a, lanes, block, c->stream));
     // the backward kernel splits the wheels over the same lanes
     if (c->timing) HIP_TRY(c, hipEventRecord(c->ev0, c->stream));
-    HIP_TRY(c, plan::launch_adjoint_backward(a, C, ckpt, weight_dev, seg, grad_dev, lanes,
-                                             c->stream));
+    if (linear)
+        HIP_TRY(c, plan::launch_adjoint_linear(a, C, ckpt, weight_dev, grad_dev, c->stream));
+    else
+        HIP_TRY(c, plan::launch_adjoint_backward(a, C, ckpt, weight_dev, seg, grad_dev, lanes,
+                                                 c->stream));
     if (c->timing) {
         HIP_TRY(c, hipEventRecord(c->ev1, c->stream));
         c->ev_recorded = true;

@@ -293,6 +293,13 @@ hipError_t launch_adjoint_backward(const RolloutArgs &a, int C, const float *ckp
                                    const float *weight, float *scratch, float *grad, int lanes,
                                    hipStream_t s);
 
+// The same gradient with each step's linearisation formed in parallel, for
+// launches of few candidates whose segments have at most ADJOINT_LINEAR_STEPS
+// steps (C * S). The recomputed states are kept in LDS.
+constexpr int ADJOINT_LINEAR_STEPS = 160;
+hipError_t launch_adjoint_linear(const RolloutArgs &a, int C, const float *ckpt,
+                                 const float *weight, float *grad, hipStream_t s);
+
 hipError_t launch_init_state(const float *s0, float *state, float *cost, int K, hipStream_t s);
 
 // Packs the cells of a W x H grid (heights h, optional costmap c) into

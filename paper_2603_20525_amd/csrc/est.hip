@@ -30,10 +30,49 @@ __device__ __forceinline__ CellPos cell_at(const RolloutArgs &a, float Px, float
     return cell_pos(a, (Px - a.x0) * a.inv_res, (Py - a.y0) * a.inv_res);
 }
 
+// The terrain slopes at a node's CoM, requested a step before the step that
+// starts there uses them.
+struct Slopes {
+    float4 fx, fy;
+    float tx, ty;
+};
+
+__device__ __forceinline__ Slopes request_slopes(const RolloutArgs &a, float x, float y) {
+    const CellPos c = cell_at(a, x, y);
+    return Slopes{load_coefs(cell_rsrc(a), c.off, 1), load_coefs(cell_rsrc(a), c.off, 2), c.tx,
+                  c.ty};
+}
+
+// A node's running cost whose wheel costs are still in flight: it is added to
+// J during the next step, or by settle() at the end.
+struct PendingCost {
+    float L = 0.0f;
+    float4 c[4] = {};
+    float tx[4] = {}, ty[4] = {};
+};
+
+__device__ __forceinline__ void settle(const RolloutArgs &a, const PendingCost &p, float &J) {
+    float c[4];
+#pragma unroll
+    for (int w = 0; w < 4; ++w) c[w] = bil(p.c[w], p.tx[w], p.ty[w]);
+    J = fmaf(a.h, p.L + ((c[0] + c[1]) + (c[2] + c[3])), J);
+}
+
 // One forward-Euler step of the EST formulation for one candidate: the
 // running cost at the node is added to J and the state advanced in place.
+// AHEAD: node holds the slopes at the state's position and receives those at
+// the next one, which depends on the slopes, the heading and the velocity only,
+// so that their request goes out before the tires are computed; and with a
+// costmap the cost added to J is the previous node's, this one's is left in
+// pend.
+template <bool AHEAD, bool CM>
 __device__ __forceinline__ void est_step(const RolloutArgs &a, float (&st)[7], float &J,
-                                         float dd, float ax) {
+                                         float dd, float ax, Slopes &node_next, PendingCost &pend_next) {
+    // without AHEAD nothing is carried from step to step
+    Slopes own_node;
+    PendingCost own_pend;
+    Slopes &node = AHEAD ? node_next : own_node;
+    PendingCost &pend = AHEAD ? pend_next : own_pend;
     const float h = a.h;
     float x = st[0], y = st[1], psi = st[2];
     float vy = st[3], wz = st[4], delta = st[5], vx = st[6];
@@ -42,8 +81,8 @@ __device__ __forceinline__ void est_step(const RolloutArgs &a, float (&st)[7], f
     // under the CoM. With the 1-2-3 convention b_z = (sin th, -cos th sin ph,
     // cos ph cos th), so sin th = -f_x/s, cos th = sqrt(1 + f_y^2)/s,
     // sin ph = f_y/sqrt(1 + f_y^2), cos ph = 1/sqrt(1 + f_y^2).
-    const CellPos cg = cell_at(a, x, y);
-    const float Tfx = lookup<1>(a, cg), Tfy = lookup<2>(a, cg);
+    if constexpr (!AHEAD) node = request_slopes(a, x, y);
+    const float Tfx = bil(node.fx, node.tx, node.ty), Tfy = bil(node.fy, node.tx, node.ty);
     const float q = fmaf(Tfy, Tfy, 1.0f);
     const float rq = frsq(q), rs = frsq(fmaf(Tfx, Tfx, q));
     const float sth = -Tfx * rs;
@@ -62,6 +101,29 @@ __device__ __forceinline__ void est_step(const RolloutArgs &a, float (&st)[7], f
     // world velocity of the planar body velocity (v_x, v_y, 0)
     const float vWx = fmaf(R11, vx, R12 * vy);
     const float vWy = fmaf(R21, vx, R22 * vy);
+    const float x_next = fmaf(h, vWx, x), y_next = fmaf(h, vWy, y);
+    if constexpr (AHEAD) node = request_slopes(a, x_next, y_next);
+    // costmap at the four wheels, P = p + R rho with the SRB lever arms
+    auto request_costs = [&]() {
+        const float R13 = sth, R23 = -(cth * sph);
+        const float rz = -a.hR;
+        const float bx = fmaf(R13, rz, x), by = fmaf(R23, rz, y);
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const float rx = (w < 2) ? a.Lf : -a.Lr;
+            const float ry = (w & 1) ? -a.half_e : a.half_e;
+            const CellPos c = cell_at(a, fmaf(R11, rx, fmaf(R12, ry, bx)),
+                                      fmaf(R21, rx, fmaf(R22, ry, by)));
+            pend.c[w] = load_coefs(cell_rsrc(a), c.off, 3);
+            pend.tx[w] = c.tx;
+            pend.ty[w] = c.ty;
+        }
+    };
+    if constexpr (AHEAD && CM) {
+        settle(a, pend, J);
+        request_costs();
+    }
+    if constexpr (AHEAD) __builtin_amdgcn_sched_barrier(0);
     // gravity in the body frame, R^T (0, 0, -g): lateral and normal parts
     const float gBy = -a.g * R32;
     const float gBz = -a.g * R33;
@@ -85,28 +147,22 @@ __device__ __forceinline__ void est_step(const RolloutArgs &a, float (&st)[7], f
     // lateral-acceleration measure: a_y - g_y = (F_y,f + F_y,r) / M
     const float pi = fabsf(Fy * a.invM) - a.a_bar_y;
     const float mm = fmaxf(0.0f, fmaf(pi, a.inv_eps_ay, 1.0f));
-    float L = fmaf(a.w_c * dd, dd, a.w_t) + (a.sigma * mm) * mm;
-    if (a.has_costmap) {
-        // costmap at the four wheels, P = p + R rho with the SRB lever arms
-        const float R13 = sth, R23 = -(cth * sph);
-        const float rz = -a.hR;
-        const float bx = fmaf(R13, rz, x), by = fmaf(R23, rz, y);
-        float c[4];
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            const float rx = (w < 2) ? a.Lf : -a.Lr;
-            const float ry = (w & 1) ? -a.half_e : a.half_e;
-            const float Px = fmaf(R11, rx, fmaf(R12, ry, bx));
-            const float Py = fmaf(R21, rx, fmaf(R22, ry, by));
-            c[w] = lookup<3>(a, cell_at(a, Px, Py));
-        }
-        L = L + ((c[0] + c[1]) + (c[2] + c[3]));
+    const float L = fmaf(a.w_c * dd, dd, a.w_t) + (a.sigma * mm) * mm;
+    if constexpr (AHEAD && CM) {
+        pend.L = L;
+    } else if (!AHEAD && a.has_costmap) {
+        // in a block of their own: issued among the tires' instructions they
+        // cost 3 % (204 288 candidates x 800 steps, whose cells miss the L1)
+        pend.L = L;
+        request_costs();
+        settle(a, pend, J);
+    } else {
+        J = fmaf(h, L, J);
     }
-    J = fmaf(h, L, J);
 
     // forward Euler and the steering / speed limits
-    x = fmaf(h, vWx, x);
-    y = fmaf(h, vWy, y);
+    x = x_next;
+    y = y_next;
     psi = fmaf(h, wz, psi);
     vy = fmaf(h, vyd, vy);
     wz = fmaf(h, wzd, wz);
@@ -122,7 +178,42 @@ __device__ __forceinline__ void est_step(const RolloutArgs &a, float (&st)[7], f
     st[6] = vx;
 }
 
-template <int BLOCK>
+// Steps of one candidate; a candidate that reaches its goal stays frozen.
+template <bool AHEAD, bool CM>
+struct Stepper {
+    const RolloutArgs &a;
+    float (&st)[7];
+    float &J;
+    Slopes node;
+    PendingCost pend;
+
+    __device__ Stepper(const RolloutArgs &a_, float (&st_)[7], float &J_)
+        : a(a_), st(st_), J(J_) {
+        if constexpr (AHEAD) node = request_slopes(a, st[0], st[1]);
+    }
+    __device__ __forceinline__ void operator()(float u0, float u1) {
+        const float dd = clampf_nan(u0, -a.drate_max, a.drate_max);
+        const float ax = a.accel_max * clampf_nan(u1, -1.0f, 1.0f);
+        const float gdx = st[0] - a.goal_x, gdy = st[1] - a.goal_y;
+        // at the goal the test stays true
+        if (!(fmaf(gdx, gdx, gdy * gdy) <= a.goal_r2))
+            est_step<AHEAD, CM>(a, st, J, dd, ax, node, pend);
+    }
+    __device__ __forceinline__ void finish() {
+        if constexpr (AHEAD && CM) settle(a, pend, J);
+    }
+};
+
+// S1: one substep per interval; the controls are then requested four intervals
+// ahead, else one. A step waits for its slopes, and with a costmap for the
+// cells under the wheels after that, about as long as it computes; a launch of
+// up to one wave per SIMD hides neither, so it requests both a step ahead: 64
+// candidates x 60 steps 30 -> 22 us, 4 096 with a costmap 45 -> 31, 11 144 x
+// 266 with one 249 -> 164, 65 536 x 800 329 -> 268. Without a costmap that pays
+// with more waves too (131 072 x 800 402 -> 376 us, 204 288 x 800 712 -> 690);
+// with one, several waves' requests a step ahead displace each other's cells
+// (150 000 x 800: 2 460 us at the start of the step, 2 750 ahead).
+template <int BLOCK, bool S1, bool AHEAD, bool CM>
 __global__ __launch_bounds__(BLOCK) void rollout_est(const RolloutArgs a) {
     const int slot = blockIdx.x * BLOCK + threadIdx.x;
     if (slot >= a.K) return;
@@ -133,17 +224,40 @@ __global__ __launch_bounds__(BLOCK) void rollout_est(const RolloutArgs a) {
     for (int q = 0; q < 7; ++q) st[q] = a.s0[q];
     float J = 0.0f;
     const float *up = a.controls_lane ? a.controls_lane + slot : a.controls + k;
-    // uniform trip counts: a candidate that reaches the goal stays frozen
-    for (int n = 0; n < a.N; ++n) {
-        const float dd = clampf_nan(up[(2 * (size_t)n) * K], -a.drate_max, a.drate_max);
-        const float ax = a.accel_max * clampf_nan(up[(2 * (size_t)n + 1) * K], -1.0f, 1.0f);
-        for (int s = 0; s < a.S; ++s) {
-            const float gdx = st[0] - a.goal_x, gdy = st[1] - a.goal_y;
-            // a candidate at its goal is frozen, so the test stays true
-            if (fmaf(gdx, gdx, gdy * gdy) <= a.goal_r2) continue;
-            est_step(a, st, J, dd, ax);
+    constexpr int PAIRS = S1 ? 4 : 1;
+    float cu0[PAIRS], cu1[PAIRS], nu0[PAIRS], nu1[PAIRS];
+    auto request = [&](int n, float (&u0)[PAIRS], float (&u1)[PAIRS]) {
+#pragma unroll
+        for (int q = 0; q < PAIRS; ++q) {
+            const float *p = up + 2 * (size_t)min(n + q, a.N - 1) * K;
+            u0[q] = p[0];
+            u1[q] = p[K];
+        }
+    };
+    request(0, cu0, cu1);
+    Stepper<AHEAD, CM> step(a, st, J);
+    int n = 0;
+    for (; n + PAIRS - 1 < a.N; n += PAIRS) {
+        request(n + PAIRS, nu0, nu1);
+#pragma unroll
+        for (int q = 0; q < PAIRS; ++q) {
+            if constexpr (S1)
+                step(cu0[q], cu1[q]);
+            else
+                for (int s = 0; s < a.S; ++s) step(cu0[q], cu1[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < PAIRS; ++q) {
+            cu0[q] = nu0[q];
+            cu1[q] = nu1[q];
         }
     }
+    if constexpr (S1) {
+#pragma unroll
+        for (int q = 0; q < PAIRS - 1; ++q)
+            if (n + q < a.N) step(cu0[q], cu1[q]);
+    }
+    step.finish();
     const float gdx = st[0] - a.goal_x, gdy = st[1] - a.goal_y;
     J = fmaf(a.w_g, sqrtf(fmaf(gdx, gdx, gdy * gdy)), J);
     bool fin = isfinite(J);
@@ -159,16 +273,25 @@ __global__ __launch_bounds__(BLOCK) void rollout_est(const RolloutArgs a) {
 
 }  // namespace
 
-hipError_t launch_rollout_est(const RolloutArgs &a, int block, hipStream_t s) {
+hipError_t launch_rollout_est(const RolloutArgs &a, int block, bool one_wave, hipStream_t s) {
     const unsigned grid = (unsigned)(((long long)a.K + block - 1) / block);
-    if (block == 64) {
-        hipLaunchKernelGGL(rollout_est<64>, dim3(grid), dim3(64), 0, s, a);
-    } else if (block == 256) {
-        hipLaunchKernelGGL(rollout_est<256>, dim3(grid), dim3(256), 0, s, a);
-    } else {
-        return hipErrorInvalidValue;
+    const bool cm = a.has_costmap != 0, ahead = one_wave || !cm;
+#define PLAN_LAUNCH(B, ONE, REQ, CMAP)                                                         \
+    if (block == B && (a.S == 1) == ONE && ahead == REQ && cm == CMAP) {                       \
+        hipLaunchKernelGGL((rollout_est<B, ONE, REQ, CMAP>), dim3(grid), dim3(B), 0, s, a);    \
+        return hipGetLastError();                                                              \
     }
-    return hipGetLastError();
+#define PLAN_LAUNCHES(B, ONE)       \
+    PLAN_LAUNCH(B, ONE, true, false) \
+    PLAN_LAUNCH(B, ONE, true, true)  \
+    PLAN_LAUNCH(B, ONE, false, true)
+    PLAN_LAUNCHES(64, false)
+    PLAN_LAUNCHES(64, true)
+    PLAN_LAUNCHES(256, false)
+    PLAN_LAUNCHES(256, true)
+#undef PLAN_LAUNCHES
+#undef PLAN_LAUNCH
+    return hipErrorInvalidValue;
 }
 
 }  // namespace plan

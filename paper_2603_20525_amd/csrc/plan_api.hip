@@ -715,7 +715,7 @@ plan_status_t plan_rollout_est(plan_ctx *c, const float state0[7], const float *
         const plan_status_t st = order_candidates(c, a, state0[5], state0[6]);
         if (st != PLAN_OK) return st;
     }
-    HIP_TRY(c, plan::launch_rollout_est(a, block, c->stream));
+    HIP_TRY(c, plan::launch_rollout_est(a, block, ((long long)K + 63) / 64 <= c->simds, c->stream));
     if (c->timing) {
         HIP_TRY(c, hipEventRecord(c->ev1, c->stream));
         c->ev_recorded = true;

@@ -278,7 +278,7 @@ hipError_t launch_sample_controls(const SampleArgs &sa, int K, int N, float *con
 
 // Extended single-track formulation (state [7]: x, y, psi, v_y, omega_z,
 // delta, v_x): full horizon from a.s0[0..6]; a.final_state is [7][K].
-hipError_t launch_rollout_est(const RolloutArgs &a, int block, hipStream_t s);
+hipError_t launch_rollout_est(const RolloutArgs &a, int block, bool one_wave, hipStream_t s);
 
 // Slots whose entry finalizes also select their plan in the same launch
 // (fused argmin per slot): result, status and sequence number seq to

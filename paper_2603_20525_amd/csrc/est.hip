@@ -64,8 +64,9 @@ __device__ __forceinline__ void settle(const RolloutArgs &a, const PendingCost &
 // the next one, which depends on the slopes, the heading and the velocity only,
 // so that their request goes out before the tires are computed; and with a
 // costmap the cost added to J is the previous node's, this one's is left in
-// pend.
-template <bool AHEAD, bool CM>
+// pend. FAST: slip ratios of at most 1, in every candidate of the wave, take the
+// arctangent without its reciprocal and selections.
+template <bool AHEAD, bool CM, bool FAST>
 __device__ __forceinline__ void est_step(const RolloutArgs &a, float (&st)[7], float &J,
                                          float dd, float ax, Slopes &node_next, PendingCost &pend_next) {
     // without AHEAD nothing is carried from step to step
@@ -135,8 +136,17 @@ __device__ __forceinline__ void est_step(const RolloutArgs &a, float (&st)[7], f
     const float Fzr = fmaf(-a.Kzzr, gBz, a.Kzx * axb);
     // virtual-tire slip angles (v_x >= vx_min > 0) and sigmoid tire
     const float ivx = frcp(vx);
-    const float af = atan_mm(fmaf(wz, a.Lf, vy) * ivx) - delta;
-    const float ar = atan_mm(fmaf(-wz, a.Lr, vy) * ivx);
+    const float tf = fmaf(wz, a.Lf, vy) * ivx, tr = fmaf(-wz, a.Lr, vy) * ivx;
+    // (a NaN is no reason for the long form: both give NaN)
+    float af, ar;
+    if (!FAST || __builtin_expect(__any(fmaxf(fabsf(tf), fabsf(tr)) > 1.0f), 0)) {
+        af = atan_mm(tf);
+        ar = atan_mm(tr);
+    } else {
+        af = atan_small(tf);
+        ar = atan_small(tr);
+    }
+    af -= delta;
     const float Caf = a.C * af, Car = a.C * ar;
     const float Fyf = (Fzf * (-Caf * a.mu)) * frsq(fmaf(Caf, Caf, a.mu2));
     const float Fyr = (Fzr * (-Car * a.mu)) * frsq(fmaf(Car, Car, a.mu2));
@@ -179,7 +189,7 @@ __device__ __forceinline__ void est_step(const RolloutArgs &a, float (&st)[7], f
 }
 
 // Steps of one candidate; a candidate that reaches its goal stays frozen.
-template <bool AHEAD, bool CM>
+template <bool AHEAD, bool CM, bool FAST>
 struct Stepper {
     const RolloutArgs &a;
     float (&st)[7];
@@ -197,7 +207,7 @@ struct Stepper {
         const float gdx = st[0] - a.goal_x, gdy = st[1] - a.goal_y;
         // at the goal the test stays true
         if (!(fmaf(gdx, gdx, gdy * gdy) <= a.goal_r2))
-            est_step<AHEAD, CM>(a, st, J, dd, ax, node, pend);
+            est_step<AHEAD, CM, FAST>(a, st, J, dd, ax, node, pend);
     }
     __device__ __forceinline__ void finish() {
         if constexpr (AHEAD && CM) settle(a, pend, J);
@@ -213,7 +223,11 @@ struct Stepper {
 // with more waves too (131 072 x 800 402 -> 376 us, 204 288 x 800 712 -> 690);
 // with one, several waves' requests a step ahead displace each other's cells
 // (150 000 x 800: 2 460 us at the start of the step, 2 750 ahead).
-template <int BLOCK, bool S1, bool AHEAD, bool CM>
+// FAST where the vector instructions of several waves a SIMD are the bound:
+// 204 288 x 800 690 -> 597 us, 131 072 x 800 376 -> 358; one wave loses as much
+// by the branch (65 536 x 800 268 -> 274), and with a costmap the cells are the
+// bound (204 288 x 800 2 390 -> 2 480).
+template <int BLOCK, bool S1, bool AHEAD, bool CM, bool FAST>
 __global__ __launch_bounds__(BLOCK) void rollout_est(const RolloutArgs a) {
     const int slot = blockIdx.x * BLOCK + threadIdx.x;
     if (slot >= a.K) return;
@@ -235,7 +249,7 @@ __global__ __launch_bounds__(BLOCK) void rollout_est(const RolloutArgs a) {
         }
     };
     request(0, cu0, cu1);
-    Stepper<AHEAD, CM> step(a, st, J);
+    Stepper<AHEAD, CM, FAST> step(a, st, J);
     int n = 0;
     for (; n + PAIRS - 1 < a.N; n += PAIRS) {
         request(n + PAIRS, nu0, nu1);
@@ -275,16 +289,18 @@ __global__ __launch_bounds__(BLOCK) void rollout_est(const RolloutArgs a) {
 
 hipError_t launch_rollout_est(const RolloutArgs &a, int block, bool one_wave, hipStream_t s) {
     const unsigned grid = (unsigned)(((long long)a.K + block - 1) / block);
-    const bool cm = a.has_costmap != 0, ahead = one_wave || !cm;
-#define PLAN_LAUNCH(B, ONE, REQ, CMAP)                                                         \
-    if (block == B && (a.S == 1) == ONE && ahead == REQ && cm == CMAP) {                       \
-        hipLaunchKernelGGL((rollout_est<B, ONE, REQ, CMAP>), dim3(grid), dim3(B), 0, s, a);    \
-        return hipGetLastError();                                                              \
+    const bool cm = a.has_costmap != 0;
+#define PLAN_LAUNCH(B, ONE, NARROW, REQ, CMAP, FAST)                                         \
+    if (block == B && (a.S == 1) == ONE && one_wave == NARROW && cm == CMAP) {               \
+        hipLaunchKernelGGL((rollout_est<B, ONE, REQ, CMAP, FAST>), dim3(grid), dim3(B), 0, s, \
+                           a);                                                               \
+        return hipGetLastError();                                                            \
     }
-#define PLAN_LAUNCHES(B, ONE)       \
-    PLAN_LAUNCH(B, ONE, true, false) \
-    PLAN_LAUNCH(B, ONE, true, true)  \
-    PLAN_LAUNCH(B, ONE, false, true)
+#define PLAN_LAUNCHES(B, ONE)                        \
+    PLAN_LAUNCH(B, ONE, true, true, false, false)    \
+    PLAN_LAUNCH(B, ONE, true, true, true, false)     \
+    PLAN_LAUNCH(B, ONE, false, true, false, true)    \
+    PLAN_LAUNCH(B, ONE, false, false, true, false)
     PLAN_LAUNCHES(64, false)
     PLAN_LAUNCHES(64, true)
     PLAN_LAUNCHES(256, false)

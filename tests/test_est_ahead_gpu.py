@@ -56,3 +56,25 @@ def test_narrow_launch_equals_wide_one(N, S, costmap):
     Jo, fo, _ = o.est_rollout(st, u[:, :, :200])
     assert_rollout_parity(Jw[:200], fw[:, :200], Jo, fo, f"N={N} S={S}")
     pl.close()
+
+
+@pytest.mark.parametrize("vy", [11.0, 15.0, 40.0, -40.0])
+def test_sliding_candidates_narrow_equals_wide(vy):
+    """Slip ratios around and beyond 1, where wide launches leave the short
+    form of the arctangent, wave by wave."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    simds = 4 * torch.cuda.get_device_properties(0).multi_processor_count
+    Kw, N = 64 * simds + 64, 12
+    w = inputs.c2(K=Kw, N=N)
+    T = w.terrain
+    s = np.asarray(w.state0, np.float32)
+    st = np.array([s[0], s[1], s[3], vy, 0, 0, s[6]], np.float32)
+    pl = P.Planner(w.vehicle, w.cost, w.integ, Kw, N, T.W, T.H)
+    pl.set_terrain(torch.from_numpy(T.height).cuda(), T.x0, T.y0, T.res)
+    u = np.ascontiguousarray(w.controls)
+    Jw, fw = run(pl, st, u)
+    J, fs = run(pl, st, u[:, :, :700])
+    np.testing.assert_array_equal(J, Jw[:700])
+    np.testing.assert_array_equal(fs, fw[:, :700])
+    pl.close()

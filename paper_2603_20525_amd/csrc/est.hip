@@ -227,17 +227,12 @@ struct Stepper {
 // 204 288 x 800 690 -> 597 us, 131 072 x 800 376 -> 358; one wave loses as much
 // by the branch (65 536 x 800 268 -> 274), and with a costmap the cells are the
 // bound (204 288 x 800 2 390 -> 2 480).
-template <int BLOCK, bool S1, bool AHEAD, bool CM, bool FAST>
-__global__ __launch_bounds__(BLOCK) void rollout_est(const RolloutArgs a) {
-    const int slot = blockIdx.x * BLOCK + threadIdx.x;
-    if (slot >= a.K) return;
-    const int k = a.order ? min(max(a.order[slot], 0), a.K - 1) : slot;
+// Steps [from, to) of the horizon's N S for the candidate whose controls start
+// at up.
+template <bool S1, bool AHEAD, bool CM, bool FAST>
+__device__ __forceinline__ void est_steps(const RolloutArgs &a, const float *up, float (&st)[7],
+                                          float &J, long long from, long long to) {
     const size_t K = (size_t)a.K;
-    float st[7];
-#pragma unroll
-    for (int q = 0; q < 7; ++q) st[q] = a.s0[q];
-    float J = 0.0f;
-    const float *up = a.controls_lane ? a.controls_lane + slot : a.controls + k;
     constexpr int PAIRS = S1 ? 4 : 1;
     float cu0[PAIRS], cu1[PAIRS], nu0[PAIRS], nu1[PAIRS];
     auto request = [&](int n, float (&u0)[PAIRS], float (&u1)[PAIRS]) {
@@ -248,30 +243,41 @@ __global__ __launch_bounds__(BLOCK) void rollout_est(const RolloutArgs a) {
             u1[q] = p[K];
         }
     };
-    request(0, cu0, cu1);
+    int n = (int)(from / a.S);
+    const int n_to = (int)(to / a.S);
+    request(n, cu0, cu1);
     Stepper<AHEAD, CM, FAST> step(a, st, J);
-    int n = 0;
-    for (; n + PAIRS - 1 < a.N; n += PAIRS) {
-        request(n + PAIRS, nu0, nu1);
-#pragma unroll
-        for (int q = 0; q < PAIRS; ++q) {
-            if constexpr (S1)
-                step(cu0[q], cu1[q]);
-            else
-                for (int s = 0; s < a.S; ++s) step(cu0[q], cu1[q]);
-        }
-#pragma unroll
-        for (int q = 0; q < PAIRS; ++q) {
-            cu0[q] = nu0[q];
-            cu1[q] = nu1[q];
-        }
-    }
     if constexpr (S1) {
+        for (; n + PAIRS - 1 < n_to; n += PAIRS) {
+            request(n + PAIRS, nu0, nu1);
+#pragma unroll
+            for (int q = 0; q < PAIRS; ++q) step(cu0[q], cu1[q]);
+#pragma unroll
+            for (int q = 0; q < PAIRS; ++q) {
+                cu0[q] = nu0[q];
+                cu1[q] = nu1[q];
+            }
+        }
 #pragma unroll
         for (int q = 0; q < PAIRS - 1; ++q)
-            if (n + q < a.N) step(cu0[q], cu1[q]);
+            if (n + q < n_to) step(cu0[q], cu1[q]);
+    } else {
+        int s = (int)(from - (long long)n * a.S);
+        const int s_to = (int)(to - (long long)n_to * a.S);
+        for (; n <= n_to; ++n, s = 0) {
+            request(n + 1, nu0, nu1);
+            const int end = n < n_to ? a.S : s_to;
+            for (; s < end; ++s) step(cu0[0], cu1[0]);
+            cu0[0] = nu0[0];
+            cu1[0] = nu1[0];
+        }
     }
     step.finish();
+}
+
+// Terminal cost and outputs of candidate k.
+__device__ __forceinline__ void est_finish(const RolloutArgs &a, int k, const float (&st)[7],
+                                           float J) {
     const float gdx = st[0] - a.goal_x, gdy = st[1] - a.goal_y;
     J = fmaf(a.w_g, sqrtf(fmaf(gdx, gdx, gdy * gdy)), J);
     bool fin = isfinite(J);
@@ -281,7 +287,107 @@ __global__ __launch_bounds__(BLOCK) void rollout_est(const RolloutArgs a) {
     a.cost[k] = J;
     if (a.final_state) {
 #pragma unroll
-        for (int q = 0; q < 7; ++q) a.final_state[(size_t)q * K + k] = st[q];
+        for (int q = 0; q < 7; ++q) a.final_state[(size_t)q * a.K + k] = st[q];
+    }
+}
+
+template <int BLOCK, bool S1, bool AHEAD, bool CM, bool FAST>
+__global__ __launch_bounds__(BLOCK) void rollout_est(const RolloutArgs a) {
+    const int slot = blockIdx.x * BLOCK + threadIdx.x;
+    if (slot >= a.K) return;
+    const int k = a.order ? min(max(a.order[slot], 0), a.K - 1) : slot;
+    float st[7];
+#pragma unroll
+    for (int q = 0; q < 7; ++q) st[q] = a.s0[q];
+    float J = 0.0f;
+    const float *up = a.controls_lane ? a.controls_lane + slot : a.controls + k;
+    est_steps<S1, AHEAD, CM, FAST>(a, up, st, J, 0, (long long)a.N * a.S);
+    est_finish(a, k, st, J);
+}
+
+// A launch of a few waves per SIMD and a remainder lasts as long as the SIMDs
+// that take a wave more than the others (204 288 candidates: 120 of 1 024 SIMDs
+// take four, the others three). Here exactly `rounds` waves per SIMD, the
+// workers, share the groups of 64 candidates in equal parts of their steps:
+// the groups' steps in a row, group after group, are cut every `part` steps
+// (at least one horizon). A worker whose part ends inside a group
+// first runs that group up to there and hands its state on, then the whole
+// groups, and last the rest of the group that its part starts in, whose state
+// the worker before it handed on long since: it ran that piece first, and all
+// parts are as long. Were it not there in time (the workers of a launch need
+// not all be running, or have started), the worker runs the piece itself.
+// One flag a worker: 0 at rest, 1 its state is there, 2 nobody waits for it
+// any more; whoever comes last puts it back to 0.
+template <bool S1, bool FAST>
+__global__ __launch_bounds__(256) void rollout_est_parts(const RolloutArgs a, long long part,
+                                                         float *handoff, int *flag) {
+    const int worker =
+        __builtin_amdgcn_readfirstlane((int)blockIdx.x * 4 + (int)(threadIdx.x >> 6));
+    const int lane = threadIdx.x & 63;
+    const long long T = (long long)a.N * a.S;
+    const long long total = (long long)((a.K + 63) / 64) * T;
+    const long long lo = worker * part, hi = min(lo + part, total);
+    if (lo >= hi) return;
+    const int g_lo = (int)(lo / T), g_hi = (int)((hi - 1) / T);
+    const long long o_lo = lo - g_lo * T, o_hi = hi - g_hi * T;
+    const bool head = o_hi < T, tail = o_lo > 0;  // never both of one group: part >= T
+    const int first = g_lo + tail, last = g_hi - head;  // whole groups
+    const int pieces = (int)head + (last - first + 1) + (int)tail;
+    for (int p = 0; p < pieces; ++p) {
+        const bool is_head = head && p == 0, is_tail = tail && p == pieces - 1;
+        const int g = is_head ? g_hi : is_tail ? g_lo : first + p - (int)head;
+        const int slot = min(g * 64 + lane, a.K - 1);
+        const int k = a.order ? min(max(a.order[slot], 0), a.K - 1) : slot;
+        const float *up = a.controls_lane ? a.controls_lane + slot : a.controls + k;
+        float st[7];
+#pragma unroll
+        for (int q = 0; q < 7; ++q) st[q] = a.s0[q];
+        float J = 0.0f;
+        long long from = 0;
+        if (is_tail) {
+            int seen = 0;
+            for (int spin = 0; spin < 1 << 14 && seen != 1; ++spin) {
+                seen = __builtin_amdgcn_readfirstlane(__hip_atomic_load(
+                    &flag[worker - 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+                if (seen != 1) __builtin_amdgcn_s_sleep(32);
+            }
+            if (seen != 1) {
+                int none = 0;
+                if (lane == 0)
+                    __hip_atomic_compare_exchange_strong(&flag[worker - 1], &none, 2,
+                                                         __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                         __HIP_MEMORY_SCOPE_AGENT);
+                seen = __builtin_amdgcn_readfirstlane(none);
+            }
+            if (seen == 1) {
+                asm volatile("" ::: "memory");  // the state after the flag
+                float *h = handoff + (size_t)(worker - 1) * 512 + lane;
+#pragma unroll
+                for (int q = 0; q < 7; ++q)
+                    st[q] = __hip_atomic_load(h + q * 64, __ATOMIC_RELAXED,
+                                              __HIP_MEMORY_SCOPE_AGENT);
+                J = __hip_atomic_load(h + 7 * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                if (lane == 0)
+                    __hip_atomic_store(&flag[worker - 1], 0, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+                from = o_lo;
+            }
+        }
+        est_steps<S1, true, false, FAST>(a, up, st, J, from, is_head ? o_hi : T);
+        if (is_head) {
+            float *h = handoff + (size_t)worker * 512 + lane;
+#pragma unroll
+            for (int q = 0; q < 7; ++q)
+                __hip_atomic_store(h + q * 64, st[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(h + 7 * 64, J, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the flag after the state
+            if (lane == 0 && __hip_atomic_exchange(&flag[worker], 1, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT) == 2)
+                __hip_atomic_store(&flag[worker], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else if (g * 64 + lane < a.K) {
+            est_finish(a, k, st, J);
+        }
     }
 }
 
@@ -308,6 +414,24 @@ hipError_t launch_rollout_est(const RolloutArgs &a, int block, bool one_wave, hi
 #undef PLAN_LAUNCHES
 #undef PLAN_LAUNCH
     return hipErrorInvalidValue;
+}
+
+hipError_t launch_rollout_est_parts(const RolloutArgs &a, int rounds, int simds, float *handoff,
+                                    int *flag, hipStream_t s) {
+    const long long T = (long long)a.N * a.S, workers = (long long)rounds * simds;
+    const long long total = (((long long)a.K + 63) / 64) * T;
+    const long long share = (total + workers - 1) / workers;
+    const long long part = share > T ? share : T;
+    // no more workgroups of four waves fit a compute unit's 160 KB than rounds
+    const unsigned lds = 160 * 1024 / (rounds + 1) + 1024;
+    const dim3 grid((unsigned)(workers / 4));
+    if (a.S == 1)
+        hipLaunchKernelGGL((rollout_est_parts<true, true>), grid, dim3(256), lds, s, a, part,
+                           handoff, flag);
+    else
+        hipLaunchKernelGGL((rollout_est_parts<false, true>), grid, dim3(256), lds, s, a, part,
+                           handoff, flag);
+    return hipGetLastError();
 }
 
 }  // namespace plan

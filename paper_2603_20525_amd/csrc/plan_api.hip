@@ -56,6 +56,12 @@ struct plan_ctx {
     size_t ctrl_lane_floats = 0;
     // terrain preparation: intermediate grid of the separable smoothing
     float *smooth_tmp = nullptr;
+    // equal shares of the EST rollout (launch_rollout_est_parts): the waves'
+    // states and flags, used on one stream, the first that launches it
+    float *est_handoff = nullptr;
+    int *est_flag = nullptr;
+    hipStream_t est_stream = nullptr;
+    bool est_stream_set = false;
     // adjoint workspace (grown on demand): state, checkpoints, segment scratch
     float *gws = nullptr;
     size_t gws_floats = 0;
@@ -67,6 +73,8 @@ struct plan_ctx {
 };
 
 static thread_local std::string g_create_err;
+
+constexpr int EST_MAX_ROUNDS = 6;  // waves per SIMD
 
 // Fixed adjoint workspace of plan_rollout_grad_noalloc, for callers that
 // cannot allocate device memory inside a call. One copy per GPU, held until
@@ -132,6 +140,8 @@ static void release(plan_ctx *c) {
     (void)hipFree(c->sel_dev);
     (void)hipFree(c->gws);
     (void)hipFree(c->smooth_tmp);
+    (void)hipFree(c->est_handoff);
+    (void)hipFree(c->est_flag);
     (void)hipFree(c->ow.lat);
     (void)hipFree(c->ctrl_lane);
     (void)hipFree(c->ow.range);
@@ -341,6 +351,12 @@ plan_status_t plan_create(plan_ctx **out, const plan_vehicle_t *veh, const plan_
     }
     CREATE_TRY(hipMalloc(&c->ow.hist, sizeof(unsigned) * 256 * (size_t)c->ow.nt_max));
     CREATE_TRY(hipMalloc(&c->ow.dtotal, sizeof(unsigned) * 256));
+    if (((long long)max_K + 63) / 64 > c->simds) {
+        const size_t workers = (size_t)EST_MAX_ROUNDS * c->simds;
+        CREATE_TRY(hipMalloc(&c->est_handoff, sizeof(float) * 512 * workers));
+        CREATE_TRY(hipMalloc(&c->est_flag, sizeof(int) * workers));
+        CREATE_TRY(hipMemset(c->est_flag, 0, sizeof(int) * workers));
+    }
     CREATE_TRY(plan::launch_order_reset(c->ow, c->stream));
     CREATE_TRY(hipEventCreate(&c->ev0));
     CREATE_TRY(hipEventCreate(&c->ev1));
@@ -685,6 +701,37 @@ plan_status_t plan_select_sampled(plan_ctx *c, const plan_sample_t *spec, const 
     return want ? wait_result(c, seq, best_k, best_cost) : PLAN_OK;
 }
 
+// Waves per SIMD among which an EST launch shares its steps equally, or 0: it
+// gives each wave a group of 64 candidates. Sharing saves the last, partial
+// round of waves but runs the rest with one wave per SIMD fewer, which pays up
+// to a remainder that depends on how well that many waves hide each other's
+// latency. 800 steps, shared against not, in us: 66 000 candidates (1.01 waves
+// per SIMD) 274 / 345, 80 000 (1.22) 334 / 339, 90 000 (1.37) 370 / 343;
+// 137 000 (2.09) 373 / 485, 170 000 (2.59) 464 / 490, 185 000 (2.82) 501 / 499;
+// 204 288 (3.12) 521 / 616, 240 000 (3.66) 622 / 641; 270 000 (4.12) 726 / 821,
+// 300 000 (4.58) 826 / 820; 350 000 (5.34) 937 / 976; 400 000 (6.10) 1 054 /
+// 1 172. The shared form keeps state between the waves in the context, so it
+// stays on one stream and out of graphs, whose replays could overlap with other
+// launches. With a costmap the cells are the bound, not the last round.
+static int est_rounds(plan_ctx *c, int K) {
+    const int groups = (int)(((long long)K + 63) / 64), rounds = groups / c->simds;
+    const int rest = groups - rounds * c->simds;
+    if (!c->est_handoff || c->has_costmap || rounds < 1 || rounds > EST_MAX_ROUNDS || rest == 0)
+        return 0;
+    const int quarters = rounds == 1 ? 1 : rounds <= 3 ? 3 : 2;
+    if (4 * rest > quarters * c->simds) return 0;
+    if (c->est_stream_set && c->est_stream != c->stream) return 0;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &capture) != hipSuccess) {
+        (void)hipGetLastError();  // another stream's capture: not an error of this call
+        return 0;
+    }
+    if (capture != hipStreamCaptureStatusNone) return 0;
+    c->est_stream = c->stream;
+    c->est_stream_set = true;
+    return rounds;
+}
+
 plan_status_t plan_rollout_est(plan_ctx *c, const float state0[7], const float *controls_dev,
                                int K, int N, float *cost_dev, float *final_state_dev) {
     if (!c) return PLAN_EINVAL;
@@ -715,7 +762,13 @@ plan_status_t plan_rollout_est(plan_ctx *c, const float state0[7], const float *
         const plan_status_t st = order_candidates(c, a, state0[5], state0[6]);
         if (st != PLAN_OK) return st;
     }
-    HIP_TRY(c, plan::launch_rollout_est(a, block, ((long long)K + 63) / 64 <= c->simds, c->stream));
+    const int rounds = est_rounds(c, K);
+    if (rounds > 0)
+        HIP_TRY(c, plan::launch_rollout_est_parts(a, rounds, c->simds, c->est_handoff,
+                                                  c->est_flag, c->stream));
+    else
+        HIP_TRY(c, plan::launch_rollout_est(a, block, ((long long)K + 63) / 64 <= c->simds,
+                                            c->stream));
     if (c->timing) {
         HIP_TRY(c, hipEventRecord(c->ev1, c->stream));
         c->ev_recorded = true;

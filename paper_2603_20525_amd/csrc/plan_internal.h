@@ -279,6 +279,11 @@ hipError_t launch_sample_controls(const SampleArgs &sa, int K, int N, float *con
 // Extended single-track formulation (state [7]: x, y, psi, v_y, omega_z,
 // delta, v_x): full horizon from a.s0[0..6]; a.final_state is [7][K].
 hipError_t launch_rollout_est(const RolloutArgs &a, int block, bool one_wave, hipStream_t s);
+// The same with the steps of all candidates shared equally by rounds * simds
+// waves (a.K > 64 * simds candidates, no costmap). handoff: 512 floats, flag:
+// one int (0 at rest) for each of them.
+hipError_t launch_rollout_est_parts(const RolloutArgs &a, int rounds, int simds, float *handoff,
+                                    int *flag, hipStream_t s);
 
 // Slots whose entry finalizes also select their plan in the same launch
 // (fused argmin per slot): result, status and sequence number seq to

@@ -220,7 +220,8 @@ __host__ __device__ inline long long terrain_cells(long long W, long long H) { r
 constexpr long long MAX_TERRAIN_CELLS = 1ll << 26;
 
 // One tick of the serving loop: which slots advance through which control
-// intervals, and which blocks of the launch belong to each slot.
+// intervals, and which blocks of the launch belong to each slot; the entries
+// with the most intervals first.
 constexpr int MAX_TICK_SLOTS = 128;
 
 struct TickEntry {
@@ -233,6 +234,8 @@ struct TickEntry {
 struct TickTable {
     int count;
     int total_blocks;
+    int row;      // workgroups per round of the launch (rollout_slots)
+    int costmap;  // some slot's terrain has one
     TickEntry e[MAX_TICK_SLOTS];
 };
 

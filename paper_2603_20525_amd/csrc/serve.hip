@@ -14,6 +14,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <chrono>
 #include <deque>
 #include <new>
@@ -318,24 +319,32 @@ static plan_status_t launch_step(plan_server *s) {
     // request's latency at 200 req/s from 0.088 to 0.11 ms)
     block = (total_K * lanes + 63) / 64 < 4096 ? 64 : 256;
     Step st;
-    int blocks = 0;
     for (int i = 0; i < s->max_slots; ++i) {
         Slot &sl = s->slots[i];
         if (sl.req < 0) continue;
         const plan_request_t &r = s->reqs[sl.req].r;
         plan::TickEntry &e = t.e[t.count++];
         e.slot = i;
-        e.block_start = blocks;
         e.n0 = sl.progress;
         // a slice of `chunk` intervals while requests wait for a slot or for
         // memory; with nothing waiting, run to the horizon's end in this launch
         const int slice = s->queue.empty() ? r.N : s->chunk;
         e.n1 = sl.progress + slice < r.N ? sl.progress + slice : r.N;
         e.finalize = e.n1 == r.N;
-        blocks += (int)(((long long)r.K * lanes + block - 1) / block);
+        if (r.costmap_dev) t.costmap = 1;
         if (e.finalize) st.finished.emplace_back(i, sl.req);
     }
-    t.total_blocks = blocks;
+    std::sort(t.e, t.e + t.count, [](const plan::TickEntry &p, const plan::TickEntry &q) {
+        const int np = p.n1 - p.n0, nq = q.n1 - q.n0;
+        return np != nq ? np > nq : p.slot < q.slot;
+    });
+    for (int j = 0; j < t.count; ++j) {
+        const long long K = s->reqs[s->slots[t.e[j].slot].req].r.K;
+        t.e[j].block_start = t.total_blocks;
+        t.total_blocks += (int)((K * lanes + block - 1) / block);
+    }
+    // a round gives every SIMD a wave
+    t.row = s->simds * 64 / block;
     // the requests that end in this launch select their plans in it and
     // write their results into this step's pinned ring entry
     st.ring = s->ring_next;

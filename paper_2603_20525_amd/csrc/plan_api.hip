@@ -35,7 +35,6 @@ struct plan_ctx {
     float x0 = 0, y0 = 0, res = 0;
     bool has_terrain = false;
     bool has_costmap = false;
-    int *bad_dev = nullptr;
     int *bad_host = nullptr;  // pinned
     // selection workspace
     unsigned long long *part_keys = nullptr;  // argmin slot, all ones between launches
@@ -133,7 +132,6 @@ static void release(plan_ctx *c) {
     if (!c) return;
     if (c->stream) (void)hipStreamSynchronize(c->stream);
     (void)hipFree(c->cells);
-    (void)hipFree(c->bad_dev);
     (void)hipFree(c->part_keys);
     (void)hipFree(c->counters);
     (void)hipFree(c->fused_key);
@@ -330,7 +328,6 @@ plan_status_t plan_create(plan_ctx **out, const plan_vehicle_t *veh, const plan_
     CREATE_TRY(resolve_scratch(c->device));
     CREATE_TRY(hipMalloc(&c->cells, sizeof(float4) * 4 * plan::terrain_cells(max_W, max_H)));
     CREATE_TRY(hipMalloc(&c->smooth_tmp, sizeof(float) * (size_t)max_W * max_H));
-    CREATE_TRY(hipMalloc(&c->bad_dev, sizeof(int)));
     CREATE_TRY(hipHostMalloc(&c->bad_host, sizeof(int), hipHostMallocDefault));
     CREATE_TRY(hipMalloc(&c->part_keys, sizeof(unsigned long long)));
     CREATE_TRY(hipMemset(c->part_keys, 0xFF, sizeof(unsigned long long)));
@@ -389,13 +386,14 @@ plan_status_t plan_set_terrain(plan_ctx *c, const float *height_dev, int W, int 
         return fail(c, PLAN_EINVAL, "terrain origin/resolution invalid");
     HIP_TRY(c, hipSetDevice(c->device));
     c->has_terrain = false;
-    HIP_TRY(c, hipMemsetAsync(c->bad_dev, 0, sizeof(int), c->stream));
+    // the kernel reports straight to host memory: clearing a device flag and
+    // copying it back cost 3 us a map
+    *c->bad_host = 0;  // no kernel of an earlier call is left: each was waited for
     HIP_TRY(c, plan::launch_pack_terrain(height_dev, costmap_dev, W, H, 1.0f / res, c->cells,
-                                         c->bad_dev, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(c->bad_host, c->bad_dev, sizeof(int), hipMemcpyDeviceToHost,
-                              c->stream));
+                                         c->bad_host, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
-    if (*c->bad_host) return fail(c, PLAN_EINVAL, "terrain holds non-finite values");
+    if (__atomic_load_n(c->bad_host, __ATOMIC_ACQUIRE))
+        return fail(c, PLAN_EINVAL, "terrain holds non-finite values");
     c->W = W;
     c->H = H;
     c->x0 = x0;

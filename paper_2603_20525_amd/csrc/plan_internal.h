@@ -311,7 +311,7 @@ hipError_t launch_adjoint_linear(const RolloutArgs &a, int C, const float *ckpt,
 hipError_t launch_init_state(const float *s0, float *state, float *cost, int K, hipStream_t s);
 
 // Packs the cells of a W x H grid (heights h, optional costmap c) into
-// cells; *bad is set if any node is not finite.
+// cells; *bad, in host memory, is set to 1 if any node is not finite.
 hipError_t launch_pack_terrain(const float *h, const float *c, int W, int H, float inv_res,
                                float4 *cells, int *bad, hipStream_t s);
 

@@ -32,7 +32,7 @@ __global__ __launch_bounds__(256) void pack_terrain(const float *__restrict__ hg
     __shared__ PackLds lds;
     if (!pack_tile(hgt, cm, W, H, inv_res, blockIdx.x * PACK_TILE, blockIdx.y * PACK_TILE,
                    cells, lds))
-        atomicOr(bad, 1);
+        __hip_atomic_store(bad, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // ---------------------------------------------------------------- argmin ----

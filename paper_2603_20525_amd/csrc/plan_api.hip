@@ -983,10 +983,10 @@ static plan_status_t grad_launch(plan_ctx *c, const float *state0, const float *
     int C = checkpoint_every < N ? checkpoint_every : N;
     // Up to 24 candidates per compute unit (six rounds of workgroups of four)
     // the backward pass whose steps are linearised in parallel is faster: N =
-    // 100, C = 10, with the forward pass, against the serial one: K = 16 87
-    // against 257 us, 1 024 105 against 267, 4 096 233 against 288, 6 000 291
-    // against 296; 8 192 294 against 292, 16 384 491 against 309 (that one's
-    // waves have SIMDs to themselves up to there).
+    // 100, C = 10, with the forward pass, against the serial one: K = 16 80
+    // against 237 us, 1 024 83 against 245, 4 096 213 against 265, 6 000 224
+    // against 270; at 8 192 they are even (270), at 16 384 the serial one is 1.6
+    // times as fast (its waves have SIMDs to themselves up to there).
     const int fine = linear_interval(N, C, c->integ.substeps);
     const bool linear = K <= 6 * c->simds &&
                         (long long)fine * c->integ.substeps <= plan::ADJOINT_LINEAR_STEPS;
@@ -1012,9 +1012,13 @@ static plan_status_t grad_launch(plan_ctx *c, const float *state0, const float *
     auto_launch(K, c->simds, &lanes, &block);
     if (c->lanes_opt) lanes = c->lanes_opt;
     if (c->block_opt) block = c->block_opt;
+    const long long waves = ((long long)K * lanes + 63) / 64;
+    const bool one_wave = waves <= c->simds;
+    if (!c->block_opt && lanes > 1 && plan::steps_ahead(a, one_wave) && 4 * waves <= c->simds)
+        block = 64;  // as in launch()
     c->last_lanes = lanes;
     c->last_block = block;
-    HIP_TRY(c, plan::launch_rollout_ckpt(a, lanes, block, c->stream));
+    HIP_TRY(c, plan::launch_rollout_ckpt(a, lanes, block, c->stream, one_wave));
     // the backward kernel splits the wheels over the same lanes
     if (c->timing) HIP_TRY(c, hipEventRecord(c->ev0, c->stream));
     if (linear)

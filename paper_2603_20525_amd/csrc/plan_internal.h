@@ -253,7 +253,8 @@ hipError_t launch_rollout(const RolloutArgs &a, int lanes, int block, bool chunk
 
 // Full-horizon rollout that also stores every candidate's state at each
 // checkpoint (a.ckpt, a.ckpt_every): the adjoint's forward pass in one launch.
-hipError_t launch_rollout_ckpt(const RolloutArgs &a, int lanes, int block, hipStream_t s);
+hipError_t launch_rollout_ckpt(const RolloutArgs &a, int lanes, int block, hipStream_t s,
+                               bool one_wave = false);
 
 // Full-horizon rollout whose last workgroup to finish also selects the argmin
 // (a.sel_* and a.plan), with controls read (sampled = false) or drawn.

@@ -76,7 +76,9 @@ hipError_t launch_rollout_sampled(const RolloutArgs &a, int lanes, int block, hi
     return one_wave ? launch_sampled_1wave(a, block, s) : launch_sampled_lanes<1>(a, block, s);
 }
 
-hipError_t launch_rollout_ckpt(const RolloutArgs &a, int lanes, int block, hipStream_t s) {
+hipError_t launch_rollout_ckpt(const RolloutArgs &a, int lanes, int block, hipStream_t s,
+                               bool one_wave) {
+    if (lanes != 1 && steps_ahead(a, one_wave)) return launch_ckpt_multi_1wave(a, lanes, block, s);
     return lanes == 1 ? launch_ckpt_lanes<1>(a, block, s) : launch_ckpt_multi(a, lanes, block, s);
 }
 

@@ -39,7 +39,7 @@ template <int LANES, bool CHUNK, bool SAMPLED = false, bool RK4 = false, bool CK
 __device__ __forceinline__ float simulate(const RolloutArgs &a, int k, int sub, bool store,
                                           const float *up) {
     constexpr int WPL = 4 / LANES;  // wheels per lane
-    constexpr bool AHEAD = REQUEST_AHEAD && !RK4 && !CKPT && S1;
+    constexpr bool AHEAD = REQUEST_AHEAD && !RK4 && S1 && (!CKPT || LANES > 1);
     constexpr bool TRIPS = AHEAD && LANES > 1;  // the loop of four-interval trips below
     const size_t K = (size_t)a.K;
 
@@ -107,14 +107,14 @@ __device__ __forceinline__ float simulate(const RolloutArgs &a, int k, int sub, 
     // CKPT: ckpt[b] = state at interval min(b C, N), the 13 stores spread over
     // the lane group; a candidate past its goal exit keeps its frozen state
     int ckpt_done = 0;
-    auto write_ckpt = [&](int b) {
+    auto write_ckpt = [&](int b, const float (&s)[13]) {
         if (!store) return;
         float *c = a.ckpt + (size_t)b * 13 * K + k;
 #pragma unroll
         for (int q = 0; q < 13; ++q)
-            if ((q & (LANES - 1)) == sub) c[(size_t)q * K] = st[q];
+            if ((q & (LANES - 1)) == sub) c[(size_t)q * K] = s[q];
     };
-    if constexpr (CKPT) write_ckpt(0);
+    if constexpr (CKPT) write_ckpt(0, st);
 
     // Euler with one substep per interval in a request-ahead build: the
     // terrain of each node is requested a step ahead. The loop
@@ -147,6 +147,8 @@ __device__ __forceinline__ float simulate(const RolloutArgs &a, int k, int sub, 
 #pragma unroll
         for (int q = 0; q < 13; ++q) kept[q] = st[q];
         kept[13] = J;
+        // the one at N is written below, with the final state
+        int until_ckpt = CKPT ? a.ckpt_every : 0;
         auto interval = [&](float dd, float ax, const NodeRequest<LANES, CM> &cur,
                             NodeRequest<LANES, CM> &nxt) {
             // goal test at the node, written as in the other loops so that a
@@ -160,6 +162,15 @@ __device__ __forceinline__ float simulate(const RolloutArgs &a, int k, int sub, 
                 done = done || arrives;
             }
             euler_step_ahead<LANES, CM>(a, arms, st, J, dd, ax, cur, nxt);
+            if constexpr (CKPT) {
+                if (__builtin_expect(--until_ckpt == 0, 0)) {
+                    until_ckpt = a.ckpt_every;
+                    float s[13];
+#pragma unroll
+                    for (int q = 0; q < 13; ++q) s[q] = done ? kept[q] : st[q];
+                    write_ckpt(++ckpt_done, s);
+                }
+            }
         };
         constexpr int PER = 4 / LANES;  // pairs of a trip that a lane holds
         float cu0[PER], cu1[PER], nu0[PER], nu1[PER];
@@ -334,14 +345,14 @@ __device__ __forceinline__ float simulate(const RolloutArgs &a, int k, int sub, 
         if constexpr (CKPT) {
             if ((n + 1) % a.ckpt_every == 0 && n + 1 < a.N) {
                 ckpt_done = (n + 1) / a.ckpt_every;
-                write_ckpt(ckpt_done);
+                write_ckpt(ckpt_done, st);
             }
         }
     }
     }
     if constexpr (CKPT) {
         const int nseg = (a.N + a.ckpt_every - 1) / a.ckpt_every;
-        for (int b = ckpt_done + 1; b <= nseg; ++b) write_ckpt(b);
+        for (int b = ckpt_done + 1; b <= nseg; ++b) write_ckpt(b, st);
     }
 
     if (a.finalize) {
@@ -691,6 +702,7 @@ hipError_t launch_rollout_multi_1wave(const RolloutArgs &a, int lanes, int block
 hipError_t launch_sampled_multi_1wave(const RolloutArgs &a, int lanes, int block, hipStream_t s);
 hipError_t launch_argmin_multi_1wave(const RolloutArgs &a, int lanes, int block, bool sampled,
                                      hipStream_t s);
+hipError_t launch_ckpt_multi_1wave(const RolloutArgs &a, int lanes, int block, hipStream_t s);
 hipError_t launch_slots_multi_1wave(const RolloutArgs *slots, const TickTable &t, int *bad,
                                     SelectOut *ring, uint32_t seq, int lanes, int block,
                                     hipStream_t s);

@@ -51,6 +51,26 @@ hipError_t launch_argmin_multi_1wave(const RolloutArgs &a, int lanes, int block,
                    : launch_any<false, false, true>(a, lanes, block, s);
 }
 
+hipError_t launch_ckpt_multi_1wave(const RolloutArgs &a, int lanes, int block, hipStream_t s) {
+    const unsigned grid = (unsigned)(((long long)a.K * lanes + block - 1) / block);
+#define PLAN_LAUNCH(L, B, CMAP)                                                                 \
+    if (lanes == L && block == B && (a.has_costmap != 0) == CMAP) {                             \
+        hipLaunchKernelGGL((rollout_srb<L, B, false, false, false, false, true, true, CMAP>),    \
+                           dim3(grid), dim3(B), 0, s, a);                                       \
+        return hipGetLastError();                                                               \
+    }
+    PLAN_LAUNCH(2, 64, false)
+    PLAN_LAUNCH(2, 64, true)
+    PLAN_LAUNCH(2, 256, false)
+    PLAN_LAUNCH(2, 256, true)
+    PLAN_LAUNCH(4, 64, false)
+    PLAN_LAUNCH(4, 64, true)
+    PLAN_LAUNCH(4, 256, false)
+    PLAN_LAUNCH(4, 256, true)
+#undef PLAN_LAUNCH
+    return hipErrorInvalidValue;
+}
+
 hipError_t launch_slots_multi_1wave(const RolloutArgs *slots, const TickTable &t, int *bad,
                                     SelectOut *ring, uint32_t seq, int lanes, int block,
                                     hipStream_t s) {

@@ -109,3 +109,23 @@ def test_chunks_and_goal_at_the_start(case, lanes):
     at_goal[1] += 0.35 * st[6] * np.sin(st[5])
     J, fs = run(pl, at_goal, u, K, N, None, lanes, 64)
     assert (fs == at_goal.astype(np.float32)[:, None]).all() and np.unique(J).size == 1
+
+
+# checkpoints at, between and past the ends of trips, and at the horizon's end
+@pytest.mark.parametrize("C", [1, 3, 4, 7, 20, 21])
+@pytest.mark.parametrize("N", [3, 20, 21])
+def test_checkpoints_equal_general_loop(case, N, C):
+    """Costs and gradients of launches whose backward pass is the serial one
+    either way: it starts every segment from a checkpoint."""
+    pl, st, u, Kw = case
+    res = []
+    for K in (Kw, (Kw - 64) // 4 + 3):  # 8 candidates per SIMD: one wave, serial backward
+        ud = torch.from_numpy(np.ascontiguousarray(u[:N, :, :K])).cuda()
+        pl.set_launch(4, 64)
+        J, g = torch.empty(K, device="cuda"), torch.empty(N, 2, K, device="cuda")
+        pl.rollout_grad(st, ud, J, g, None, C)
+        torch.cuda.synchronize()
+        pl.set_launch(0, 0)
+        res.append((J.cpu().numpy(), g.cpu().numpy(), K))
+    (Jw, gw, _), (J, g, K) = res
+    same((J, g), (Jw[:K], gw[:, :, :K]), f"N={N} C={C}")

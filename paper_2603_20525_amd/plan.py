@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import struct
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libplan.so")
@@ -523,6 +524,14 @@ class Result(C.Structure):
                 ("t_done", C.c_double)]
 
 
+# The two structs' layouts for one packing call instead of a ctypes store per
+# field (submission 3.0 -> 2.4 us, result 1.0 -> 0.7)
+_REQUEST = struct.Struct("@Pii3fP13fPii10ffiffiPP")
+_RESULT = struct.Struct("@iifi3d")
+_RESULT_NAMES = tuple(n for n, _ in Result._fields_)
+assert _REQUEST.size == C.sizeof(Request) and _RESULT.size == C.sizeof(Result)
+
+
 SERVER_EXPORTS = ("plan_server_create", "plan_server_submit", "plan_server_step",
                   "plan_server_drain", "plan_server_stats", "plan_server_result",
                   "plan_server_completions", "plan_server_now", "plan_server_destroy",
@@ -570,8 +579,8 @@ class Server:
     def __init__(self, vehicle, max_slots, max_K, max_N, max_W, max_H, budget_bytes,
                  chunk_intervals=16, stream=None):
         import torch
-        self._req = Request()
-        self._rid = C.c_int(-1)
+        self._req, self._rid, self._res = Request(), C.c_int(-1), Result()
+        self._refs = C.byref(self._req), C.byref(self._rid), C.byref(self._res)
         self._params = {}
         self._cbuf = {}
         self._cn, self._sa, self._sq = C.c_int(0), C.c_int(0), C.c_int(0)
@@ -585,6 +594,7 @@ class Server:
         _scheck("plan_server_create", st, None)
         self.h = h
         self._keep = {}
+        self._calls = L.plan_server_submit, L.plan_server_result
 
     def submit(self, height, x0, y0, res, state0, controls, cost, integ, plan, costmap=None,
                costs_out=None):
@@ -593,37 +603,47 @@ class Server:
         H, W = height.shape
         N, two, K = controls.shape
         # the library copies the request, so one Request object is reused
-        r = self._req
-        r.height_dev = _dptr(height, "height")
-        r.W, r.H = W, H
-        r.x0, r.y0, r.res = float(x0), float(y0), float(res)
-        r.costmap_dev = None if costmap is None else _dptr(costmap, "costmap", H * W)
-        r.state0[:] = state0
-        r.controls_dev = _dptr(controls, "controls")
-        r.K, r.N = K, N
-        r.cost = self._param(Cost, cost)
-        r.integ = self._param(Integ, integ)
-        r.plan_dev = _dptr(plan, "plan", 2 * N)
-        r.cost_dev = None if costs_out is None else _dptr(costs_out, "costs_out", K)
-        rid = self._rid
-        _scheck("plan_server_submit", _bind_server().plan_server_submit(self.h, C.byref(r),
-                                                                         C.byref(rid)), self.h)
-        self._keep[rid.value] = (height, controls, plan, costmap, costs_out)
-        return rid.value
+        ptrs = (_dptr(height, "height"),
+                None if costmap is None else _dptr(costmap, "costmap", H * W),
+                _dptr(controls, "controls"), _dptr(plan, "plan", 2 * N),
+                None if costs_out is None else _dptr(costs_out, "costs_out", K))
+        c, i = self._param(Cost, cost), self._param(Integ, integ)
+        try:
+            _REQUEST.pack_into(self._req, 0, ptrs[0], W, H, x0, y0, res, ptrs[1] or 0, *state0,
+                               ptrs[2], K, N, *c, *i, ptrs[3], ptrs[4] or 0)
+        except (struct.error, OverflowError, TypeError):
+            # field by field: a value out of a float's range, a wrong length
+            r = self._req
+            r.height_dev, r.W, r.H = ptrs[0], W, H
+            r.x0, r.y0, r.res = float(x0), float(y0), float(res)
+            r.costmap_dev = ptrs[1]
+            r.state0[:] = state0
+            r.controls_dev, r.K, r.N = ptrs[2], K, N
+            r.cost, r.integ = Cost(*c), Integ(*i)
+            r.plan_dev, r.cost_dev = ptrs[3], ptrs[4]
+        req, rid, _ = self._refs
+        st = self._calls[0](self.h, req, rid)
+        if st != PLAN_OK:
+            _scheck("plan_server_submit", st, self.h)
+        n = self._rid.value
+        self._keep[n] = (height, controls, plan, costmap, costs_out)
+        return n
 
     def _param(self, cls, d):
-        """ctypes copy of a parameter dict, reused while the dict's values are
-        unchanged (requests usually share their cost and integration dicts)."""
+        """Field values of a parameter dict as the struct holds them, reused
+        while the dict's values are unchanged (requests usually share their
+        cost and integration dicts)."""
         key = (cls, id(d))
         snap = tuple(d.values())
         hit = self._params.get(key)
         if hit is not None and hit[0] is d and hit[1] == snap:
             return hit[2]
         st = _struct(cls, d)
+        vals = tuple(getattr(st, n) for n, _ in cls._fields_)
         if len(self._params) > 256:
             self._params.clear()
-        self._params[key] = (d, snap, st)
-        return st
+        self._params[key] = (d, snap, vals)
+        return vals
 
     def step(self):
         a, q = self._sa, self._sq
@@ -641,10 +661,10 @@ class Server:
         _scheck("plan_server_drain", _bind_server().plan_server_drain(self.h), self.h)
 
     def result(self, rid) -> dict:
-        r = Result()
-        _scheck("plan_server_result", _bind_server().plan_server_result(self.h, int(rid),
-                                                                         C.byref(r)), self.h)
-        out = {n: getattr(r, n) for n, _ in Result._fields_}
+        st = self._calls[1](self.h, int(rid), self._refs[2])
+        if st != PLAN_OK:
+            _scheck("plan_server_result", st, self.h)
+        out = dict(zip(_RESULT_NAMES, _RESULT.unpack_from(self._res)))
         if out["status"] != 0:
             self._keep.pop(rid, None)
         return out

@@ -143,8 +143,8 @@ __device__ __forceinline__ void est_step(const RolloutArgs &a, float (&st)[7], f
         af = atan_mm(tf);
         ar = atan_mm(tr);
     } else {
-        af = atan_small(tf);
-        ar = atan_small(tr);
+        af = atan_mm<false, true>(tf);
+        ar = atan_mm<false, true>(tr);
     }
     af -= delta;
     const float Caf = a.C * af, Car = a.C * ar;

@@ -47,16 +47,6 @@ __device__ __forceinline__ float group_lane(float v, int i) {
     return __int_as_float(r);
 }
 
-__device__ __forceinline__ float atan_poly(float t) {
-    float p = 7.331810426e-03f;
-    p = fmaf(p, t, -3.539908305e-02f);
-    p = fmaf(p, t, 8.204584569e-02f);
-    p = fmaf(p, t, -1.339402497e-01f);
-    p = fmaf(p, t, 1.986153722e-01f);
-    p = fmaf(p, t, -3.332552314e-01f);
-    return p;
-}
-
 // Arctangent of the slip angles: x + x^3 P(x^2) on [0, 1], P of degree 5
 // with coefficients that minimise the largest absolute error over the
 // interval (a discrete minimax fit solved as a linear program; fit_atan.py in
@@ -67,23 +57,23 @@ __device__ __forceinline__ float atan_poly(float t) {
 // atan(+-inf) = +-pi/2. NAN_TO_ZERO: a NaN argument gives 0 (|x| is taken
 // as the IEEE maximum of |x| and 0, which returns 0 for a NaN), the slip
 // ratio's 0/0 convention at no extra instruction; otherwise NaN gives NaN.
-template <bool NAN_TO_ZERO = false>
+// SMALL: the caller knows |x| <= 1 or NaN; no reciprocal and no selections, the
+// same bits.
+template <bool NAN_TO_ZERO = false, bool SMALL = false>
 __device__ __forceinline__ float atan_mm(float x) {
     const float ax = NAN_TO_ZERO ? fmaxf(fabsf(x), 0.0f) : fabsf(x);
-    const bool big = ax > 1.0f;
+    const bool big = !SMALL && ax > 1.0f;
     const float r = big ? frcp(ax) : ax;
     const float t = r * r;
-    const float p = atan_poly(t);
+    float p = 7.331810426e-03f;
+    p = fmaf(p, t, -3.539908305e-02f);
+    p = fmaf(p, t, 8.204584569e-02f);
+    p = fmaf(p, t, -1.339402497e-01f);
+    p = fmaf(p, t, 1.986153722e-01f);
+    p = fmaf(p, t, -3.332552314e-01f);
     float y = fmaf(r * t, p, r);
     y = big ? 1.57079632679489662f - y : y;
     return copysignf(y, x);
-}
-
-// atan_mm's result, bit for bit, for |x| <= 1 or NaN: no reciprocal and no
-// selections.
-__device__ __forceinline__ float atan_small(float x) {
-    const float r = fabsf(x), t = r * r;
-    return copysignf(fmaf(r * t, atan_poly(t), r), x);
 }
 
 // IEEE 754-2019 maximum and minimum (v_maximum3_f32, v_minimum3_f32): a NaN

@@ -255,12 +255,16 @@ bool finite_all(const float *p, int n) {
 }
 
 void auto_launch(long long K, int simds, int *lanes, int *block) {
-    // Spread small candidate sets over more lanes (wheel-parallel); sets
-    // that give every SIMD a wave at one lane per candidate (65 536 on the
-    // MI355X's 1 024 SIMDs) use one lane, avoiding redundant chassis work.
+    // Spread small candidate sets over more lanes (wheel-parallel) as long as
+    // that gives no SIMD a second wave (on the MI355X's 1 024 SIMDs: four lanes
+    // up to 16 384 candidates, two up to 32 768): two waves of half the lanes'
+    // work last longer than one of the whole. 33 000 candidates, 100 steps, two
+    // lanes against one: 118 and 102 us, with a costmap 129 and 107; Runge-Kutta
+    // x 50 198 and 171; 65 000: 129 and 109, 140 and 122, 201 and 172; 30 000,
+    // where two lanes are one wave: 74 and 100, 77 and 117, 121 and 170.
     if (K <= 16384) {
         *lanes = 4;
-    } else if (K < 65536) {
+    } else if (K <= 32768) {
         *lanes = 2;
     } else {
         *lanes = 1;

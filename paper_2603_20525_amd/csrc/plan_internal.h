@@ -248,6 +248,9 @@ struct TickTable {
 inline bool steps_ahead(const RolloutArgs &a, bool one_wave) {
     return one_wave && a.S == 1 && a.method == 0;
 }
+inline bool stages_ahead(const RolloutArgs &a, bool one_wave) {
+    return one_wave && a.method == 1;
+}
 hipError_t launch_rollout(const RolloutArgs &a, int lanes, int block, bool chunk, hipStream_t s,
                           bool one_wave = false);
 

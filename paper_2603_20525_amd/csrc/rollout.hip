@@ -62,8 +62,9 @@ __global__ __launch_bounds__(256) void init_state(const RolloutArgs a) {
 hipError_t launch_rollout(const RolloutArgs &a, int lanes, int block, bool chunk,
                           hipStream_t s, bool one_wave) {
     if (lanes != 1)
-        return steps_ahead(a, one_wave) ? launch_rollout_multi_1wave(a, lanes, block, chunk, s)
-                                        : launch_rollout_multi(a, lanes, block, chunk, s);
+        return steps_ahead(a, one_wave) || stages_ahead(a, one_wave)
+                   ? launch_rollout_multi_1wave(a, lanes, block, chunk, s)
+                   : launch_rollout_multi(a, lanes, block, chunk, s);
     return one_wave ? launch_rollout_1wave(a, block, chunk, s)
                     : launch_rollout_lanes<1>(a, block, chunk, s);
 }

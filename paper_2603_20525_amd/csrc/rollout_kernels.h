@@ -41,6 +41,7 @@ __device__ __forceinline__ float simulate(const RolloutArgs &a, int k, int sub, 
     constexpr int WPL = 4 / LANES;  // wheels per lane
     constexpr bool AHEAD = REQUEST_AHEAD && !RK4 && S1 && (!CKPT || LANES > 1);
     constexpr bool TRIPS = AHEAD && LANES > 1;  // the loop of four-interval trips below
+    constexpr bool RK4_AHEAD = REQUEST_AHEAD && RK4 && LANES > 1;
     const size_t K = (size_t)a.K;
 
     float st0[13];
@@ -292,6 +293,9 @@ __device__ __forceinline__ float simulate(const RolloutArgs &a, int k, int sub, 
     // uniform trip counts: a candidate that reaches the goal stays in the
     // loop frozen (its lanes skip the steps), so the loops carry no
     // per-lane exit or done-flag bookkeeping
+    NodeRequest<LANES, CM> node;
+    if constexpr (RK4_AHEAD)
+        request_node<LANES, CM>(a, arms, st[0], st[1], st[2], st[3], st[4], st[5], node);
     for (int n = a.n0; n < a.n1; ++n) {
         // zero-order hold: control n for the whole interval, restricted to the
         // admissible set (|delta_dot| <= limit, throttle in [-1, 1])
@@ -330,7 +334,9 @@ __device__ __forceinline__ float simulate(const RolloutArgs &a, int k, int sub, 
                 const float gdx = st[0] - a.goal_x, gdy = st[1] - a.goal_y;
                 if (fmaf(gdx, gdx, gdy * gdy) <= a.goal_r2) continue;
             }
-            if constexpr (RK4) {
+            if constexpr (RK4_AHEAD) {
+                rk4_step_ahead<LANES, CM>(a, arms, st, J, dd, ax, node);
+            } else if constexpr (RK4) {
                 rk4_step<LANES, CM>(a, arms, st, J, dd, ax);
             } else if constexpr (SAMPLED) {
                 euler_step<LANES, CM>(a, arms, st, J, dd, ax);

@@ -1,7 +1,8 @@
 // Two- and four-lane instantiations of the rollout kernels (see
 // rollout_kernels.h) for launches of at most one wave per SIMD with one Euler
 // step per interval: each node's terrain is requested a whole step ahead and
-// the controls a trip of four intervals ahead.
+// the controls a trip of four intervals ahead; Runge-Kutta's stages request
+// their terrain one stage ahead.
 #define PLAN_REQUEST_AHEAD 1
 #include "rollout_kernels.h"
 
@@ -25,6 +26,23 @@ hipError_t launch_lanes(const RolloutArgs &a, int block, hipStream_t s) {
     return hipErrorInvalidValue;
 }
 
+template <int L, bool CHUNK>
+hipError_t launch_rk4(const RolloutArgs &a, int block, hipStream_t s) {
+    const unsigned grid = (unsigned)(((long long)a.K * L + block - 1) / block);
+#define PLAN_LAUNCH(B, CMAP)                                                                   \
+    if (block == B && (a.has_costmap != 0) == CMAP) {                                          \
+        hipLaunchKernelGGL((rollout_srb<L, B, CHUNK, false, false, true, false, false, CMAP>),  \
+                           dim3(grid), dim3(B), 0, s, a);                                      \
+        return hipGetLastError();                                                              \
+    }
+    PLAN_LAUNCH(64, false)
+    PLAN_LAUNCH(64, true)
+    PLAN_LAUNCH(256, false)
+    PLAN_LAUNCH(256, true)
+#undef PLAN_LAUNCH
+    return hipErrorInvalidValue;
+}
+
 template <bool CHUNK, bool SAMPLED, bool FUSED>
 hipError_t launch_any(const RolloutArgs &a, int lanes, int block, hipStream_t s) {
     if (a.S != 1 || a.method != 0) return hipErrorInvalidValue;
@@ -37,6 +55,10 @@ hipError_t launch_any(const RolloutArgs &a, int lanes, int block, hipStream_t s)
 
 hipError_t launch_rollout_multi_1wave(const RolloutArgs &a, int lanes, int block, bool chunk,
                                       hipStream_t s) {
+    if (a.method == 1 && lanes == 2)
+        return chunk ? launch_rk4<2, true>(a, block, s) : launch_rk4<2, false>(a, block, s);
+    if (a.method == 1 && lanes == 4)
+        return chunk ? launch_rk4<4, true>(a, block, s) : launch_rk4<4, false>(a, block, s);
     return chunk ? launch_any<true, false, false>(a, lanes, block, s)
                  : launch_any<false, false, false>(a, lanes, block, s);
 }

@@ -574,4 +574,63 @@ __device__ __forceinline__ void rk4_step(const RolloutArgs &a, const Arm (&arms)
     apply_limits(a, st);
 }
 
+// The same step with each stage's terrain requested before the forces of the
+// stage before it, which the stage's position and angles do not need. node
+// holds the requests at the state and receives those at the next one. For lane
+// groups with a SIMD to themselves, a fifth of whose cycles were waits for
+// cells: 9 425 candidates x 60 steps over a 1 200 x 900 map 126 -> 105 us, with
+// a costmap 129 -> 107; where the cells stay in the L2, 4 096 104 -> 102, 9 425
+// 105.5 -> 104.8, 6 000 104.1 -> 105.5.
+template <int LANES, bool CM = true>
+__device__ __forceinline__ void rk4_step_ahead(const RolloutArgs &a,
+                                               const Arm (&arms)[4 / LANES], float (&st)[13],
+                                               float &J, float dd, float ax,
+                                               NodeRequest<LANES, CM> &node) {
+    NodeRequest<LANES, CM> mid;
+    float k[13], acc[13], stage[13];
+    auto request = [&](const Kin &kn, float h, NodeRequest<LANES, CM> &r) {
+        request_node<LANES, CM>(a, arms, fmaf(h, kn.vWx, st[0]), fmaf(h, kn.vWy, st[1]),
+                                fmaf(h, kn.vWz, st[2]), fmaf(h, kn.psid, st[3]),
+                                fmaf(h, kn.thd, st[4]), fmaf(h, kn.phd, st[5]), r);
+    };
+    Kin kn = kinematics(node.A, st);
+    request(kn, a.h_half, mid);
+    float L = srb_forces<LANES, CM>(a, arms, st, dd, ax, node.A, node.G, kn, k);
+    float Lacc = L;
+#pragma unroll
+    for (int q = 0; q < 13; ++q) {
+        acc[q] = k[q];
+        stage[q] = fmaf(a.h_half, k[q], st[q]);
+    }
+    kn = kinematics(mid.A, stage);
+    request(kn, a.h_half, node);
+    L = srb_forces<LANES, CM>(a, arms, stage, dd, ax, mid.A, mid.G, kn, k);
+    Lacc = fmaf(2.0f, L, Lacc);
+#pragma unroll
+    for (int q = 0; q < 13; ++q) {
+        acc[q] = fmaf(2.0f, k[q], acc[q]);
+        stage[q] = fmaf(a.h_half, k[q], st[q]);
+    }
+    kn = kinematics(node.A, stage);
+    request(kn, a.h, mid);
+    L = srb_forces<LANES, CM>(a, arms, stage, dd, ax, node.A, node.G, kn, k);
+    Lacc = fmaf(2.0f, L, Lacc);
+#pragma unroll
+    for (int q = 0; q < 13; ++q) {
+        acc[q] = fmaf(2.0f, k[q], acc[q]);
+        stage[q] = fmaf(a.h, k[q], st[q]);
+    }
+    kn = kinematics(mid.A, stage);
+    request_node<LANES, CM>(
+        a, arms, fmaf(a.h_sixth, acc[0] + kn.vWx, st[0]), fmaf(a.h_sixth, acc[1] + kn.vWy, st[1]),
+        fmaf(a.h_sixth, acc[2] + kn.vWz, st[2]), fmaf(a.h_sixth, acc[3] + kn.psid, st[3]),
+        fmaf(a.h_sixth, acc[4] + kn.thd, st[4]), fmaf(a.h_sixth, acc[5] + kn.phd, st[5]), node);
+    L = srb_forces<LANES, CM>(a, arms, stage, dd, ax, mid.A, mid.G, kn, k);
+    Lacc = Lacc + L;
+    J = fmaf(a.h_sixth, Lacc, J);
+#pragma unroll
+    for (int q = 0; q < 13; ++q) st[q] = fmaf(a.h_sixth, acc[q] + k[q], st[q]);
+    apply_limits(a, st);
+}
+
 }  // namespace plan

@@ -129,3 +129,46 @@ def test_checkpoints_equal_general_loop(case, N, C):
         res.append((J.cpu().numpy(), g.cpu().numpy(), K))
     (Jw, gw, _), (J, g, K) = res
     same((J, g), (Jw[:K], gw[:, :, :K]), f"N={N} C={C}")
+
+
+@pytest.mark.parametrize("N,S", [(1, 1), (2, 1), (7, 1), (3, 4)])
+@pytest.mark.parametrize("costmap", [False, True])
+def test_runge_kutta_equals_general_loop(N, S, costmap):
+    """Runge-Kutta's stages requested ahead (up to one wave per SIMD over two
+    or four lanes) against the step that requests each stage's cells at it."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    simds = 4 * torch.cuda.get_device_properties(0).multi_processor_count
+    Kw = 32 * simds + 64
+    w = inputs.c2(K=Kw, N=N)
+    T = w.terrain
+    st = np.asarray(w.state0)
+    # arrivals in the second step, and a start at the goal below
+    cost = dict(w.cost, goal_x=float(st[0] + 0.05 * st[6]), goal_y=float(st[1]), goal_r=0.3)
+    u = np.ascontiguousarray(w.controls).copy()
+    u[0, 0, 3] = np.nan
+    pl = P.Planner(w.vehicle, cost, dict(w.integ, dt=0.04, substeps=S, method=P.PLAN_RK4), Kw, N,
+                   T.W, T.H)
+    cm = None
+    if costmap:
+        cm = torch.from_numpy(np.random.default_rng(8).uniform(0, 3, T.height.shape)
+                              .astype(np.float32)).cuda()
+    pl.set_terrain(torch.from_numpy(T.height).cuda(), T.x0, T.y0, T.res, cm)
+    for start in (st, np.concatenate([[cost["goal_x"], cost["goal_y"]], st[2:]])):
+        wide = run(pl, start, u, Kw, N, None, 4, 64)
+        same(run(pl, start, u, Kw, N, None, 2, 256), wide, "general step")
+        for K in (5, 64, 1500):
+            for lanes, block in ((2, 64), (2, 256), (4, 64), (4, 256), (0, 0)):
+                got = run(pl, start, u, K, N, None, lanes, block)
+                same(got, (wide[0][:K], wide[1][:, :K]), f"K={K} lanes={lanes} block={block}")
+    # chunks
+    K = 200
+    ud = torch.from_numpy(np.ascontiguousarray(u[:, :, :K])).cuda()
+    wide = run(pl, st, u, Kw, N, None, 4, 64)
+    J, fs = torch.empty(K, device="cuda"), torch.empty(13, K, device="cuda")
+    pl.init_state(st, fs, J)
+    for n0, n1 in ((0, N // 2), (N // 2, N)):
+        pl.rollout_chunk(fs, J, ud, n0, n1, n1 == N)
+    torch.cuda.synchronize()
+    same((J.cpu().numpy(), fs.cpu().numpy()), (wide[0][:K], wide[1][:, :K]), "chunks")
+    pl.close()

@@ -139,7 +139,6 @@ static void release(plan_ctx *c) {
     (void)hipFree(c->gws);
     (void)hipFree(c->smooth_tmp);
     (void)hipFree(c->est_handoff);
-    (void)hipFree(c->est_flag);
     (void)hipFree(c->ow.lat);
     (void)hipFree(c->ctrl_lane);
     (void)hipFree(c->ow.range);
@@ -353,9 +352,13 @@ plan_status_t plan_create(plan_ctx **out, const plan_vehicle_t *veh, const plan_
     CREATE_TRY(hipMalloc(&c->ow.hist, sizeof(unsigned) * 256 * (size_t)c->ow.nt_max));
     CREATE_TRY(hipMalloc(&c->ow.dtotal, sizeof(unsigned) * 256));
     if (((long long)max_K + 63) / 64 > c->simds) {
-        const size_t workers = (size_t)EST_MAX_ROUNDS * c->simds;
-        CREATE_TRY(hipMalloc(&c->est_handoff, sizeof(float) * 512 * workers));
-        CREATE_TRY(hipMalloc(&c->est_flag, sizeof(int) * workers));
+        // as many workers as est_rounds can choose for max_K; the flags behind
+        // the states
+        const long long most = ((long long)max_K + 63) / 64 / c->simds;
+        const size_t workers =
+            (size_t)(most < EST_MAX_ROUNDS ? most : EST_MAX_ROUNDS) * c->simds;
+        CREATE_TRY(hipMalloc(&c->est_handoff, (sizeof(float) * 512 + sizeof(int)) * workers));
+        c->est_flag = reinterpret_cast<int *>(c->est_handoff + 512 * workers);
         CREATE_TRY(hipMemset(c->est_flag, 0, sizeof(int) * workers));
     }
     CREATE_TRY(plan::launch_order_reset(c->ow, c->stream));

@@ -58,11 +58,11 @@ ALU_PEAK_GOPS = 256 * 4 * 16 * 2.4
 # change, the figure no longer describes the kernel and is reported as null.
 # workload: (FETCH_SIZE KiB, WRITE_SIZE KiB, fetch scale, write scale, signature)
 TRAFFIC_COUNTERS = {
-    # fused kernel, one lane per candidate (c5) and four lanes (c2), 256-thread
-    # workgroups, no costmap, cell-coefficient terrain; copy calibration
-    # 262144 KiB read as 131084.54 KiB (x1.99981) and written as 262144.0 KiB (x1.0)
-    "c5": (60620.54, 273.69, 262144.0 / 131084.54, 1.0, "69ddd8a1d74f33cd"),
-    "c2": (3312.91, 20.91, 262144.0 / 131084.54, 1.0, "69ddd8a1d74f33cd"),
+    # fused kernel, one lane per candidate (c5, 256-thread workgroups) and four
+    # lanes (c2, 64), no costmap, cell-coefficient terrain; copy calibration
+    # 262144 KiB read as 131084.48 KiB (x1.99981) and written as 262144.0 KiB (x1.0)
+    "c5": (60620.05, 273.69, 262144.0 / 131084.48, 1.0, "6cbe54554e71c441"),
+    "c2": (4978.78, 32.91, 262144.0 / 131084.48, 1.0, "6cbe54554e71c441"),
 }
 ROLLOUT_SOURCES = ("rollout_step.h", "rollout_kernels.h", "rollout.hip",
                    "rollout_onelane_1wave.hip", "rollout_multilane.hip",
@@ -360,8 +360,11 @@ def rows_leg():
                                               0.25))
     edges = int(offsets[-1])
     out["costmap_2048"] = {"ms": ms, "polygons": len(polys), "edges": edges,
-                           "node_edge_tests_per_s": T.W * T.H * edges * 1e3 / ms,
-                           "alu_frac": alu(25 * T.W * T.H * edges, ms / 1e3)}
+                           # most pairs are never evaluated: a tile of nodes
+                           # skips the perimeters that cannot touch it
+                           "node_edge_pairs_per_s": T.W * T.H * edges * 1e3 / ms,
+                           "gb_per_s": 4 * T.W * T.H / ms / 1e6,
+                           "hbm_frac": 4 * T.W * T.H / ms / 1e6 / HBM_PEAK_GBS}
     # terrain pack (plan_set_terrain: slopes and the cells' bilinear
     # coefficients, with its non-finite check and the host wait for it):
     # heights and costmap read once, 64-byte cells written

@@ -17,8 +17,8 @@ namespace {
 constexpr int SEL_BLOCK = 256;
 constexpr int SEL_ITEMS = 16;                      // candidates per thread
 constexpr int SEL_CHUNK = SEL_BLOCK * SEL_ITEMS;   // candidates per block
-constexpr int SM_ROWS = 4;                         // softmin: plan entries per block
 constexpr int SM_UNROLL = 8;                       // softmin: candidates in flight per thread
+constexpr int SM_GROUPS = 256;                     // softmin: compute units of the chip
 constexpr int SM_BLOCK = 1024;                     // softmin: threads per block
 
 // --------------------------------------------------------------- terrain ----
@@ -90,24 +90,75 @@ __global__ __launch_bounds__(SEL_BLOCK) void select_argmin(
 }
 
 // MPPI-style softmin in one launch with no traffic between workgroups.
-// Workgroup g owns plan entries [g*SM_ROWS, (g+1)*SM_ROWS) of the 2N. Every
+// Workgroup g owns plan entries [g ROWS, (g+1) ROWS) of the 2N. Every
 // workgroup takes the minimum key over all K itself (the costs are a few KB,
 // served from L2), weighs each finite candidate w_k = exp(-(J_k - J_min) /
 // lambda), and forms its entries' weighted sums of the clamped controls and
 // the weight sum, each thread over a fixed stride of candidates and then in
-// a fixed reduction tree, so the result does not depend on scheduling.
-// Workgroup 0 publishes (k*, J*).
+// a fixed reduction tree, so the result depends neither on scheduling nor on
+// ROWS. Workgroup 0 publishes (k*, J*).
+//
+// What bounds it at a few thousand candidates is latency: the costs, the
+// reduction, the controls. So all loads of a pass of SM_UNROLL candidates a
+// thread are issued before any is used, and with one or two entries a workgroup
+// the first pass's controls before the minimum is formed (with four that holds
+// more registers and costs: K = 4 096, N = 1 000 14.5 -> 21.8 us). K = 10 007,
+// N = 73, 5.8 MB of controls: 10.9 -> 6.9 us, 0.85 TB/s.
+template <int ROWS>
 __global__ __launch_bounds__(SM_BLOCK) void select_softmin(
     const float *__restrict__ cost, int K, const float *__restrict__ controls, int N,
     float drate_max, float inv_lambda, float *__restrict__ plan, SelectOut *__restrict__ out,
     SelectOut *out_host, uint32_t seq) {
     __shared__ unsigned long long kred[SM_BLOCK / 64];
-    __shared__ float fred[SM_BLOCK / 64][SM_ROWS + 1];
+    __shared__ float fred[SM_BLOCK / 64][ROWS + 1];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int rows = 2 * N;
+    const int r0 = blockIdx.x * ROWS;
+    float J[SM_UNROLL], u[ROWS][SM_UNROLL];
+    // candidates kb, kb + SM_BLOCK, ...: their costs and their plan entries
+    auto load_cost = [&](int kb, int q) {
+        const int k = kb + q * SM_BLOCK;
+        J[q] = k < K ? cost[k] : __builtin_inff();
+    };
+    auto load_control = [&](int kb, int q) {
+        const int k = kb + q * SM_BLOCK;
+#pragma unroll
+        for (int j = 0; j < ROWS; ++j) {
+            const int r = r0 + j;
+            u[j][q] = (k < K && r < rows) ? controls[(size_t)r * K + k] : 0.0f;
+        }
+    };
+    auto load_costs = [&](int kb) {
+#pragma unroll
+        for (int q = 0; q < SM_UNROLL; ++q) load_cost(kb, q);
+    };
+    auto load_controls = [&](int kb) {
+#pragma unroll
+        for (int q = 0; q < SM_UNROLL; ++q) load_control(kb, q);
+    };
+    float jmin = 0.0f;
+    auto weight = [&](float j) {
+        return isfinite(j) ? __expf(-(j - jmin) * inv_lambda) : 0.0f;
+    };
     unsigned long long key = ~0ull;
-    for (int k = tid; k < K; k += SM_BLOCK) {
-        const unsigned long long kk = cost_key(cost[k], k);
-        key = kk < key ? kk : key;
+    constexpr int STRIDE = SM_BLOCK * SM_UNROLL;
+    if constexpr (ROWS < 4) {
+        // the last pass first, so that the first one's costs stay for the weights
+        for (int kb = tid + (K - 1) / STRIDE * STRIDE; kb >= tid; kb -= STRIDE) {
+            load_costs(kb);
+            if (kb == tid) load_controls(kb);
+#pragma unroll
+            for (int q = 0; q < SM_UNROLL; ++q) {
+                const int k = kb + q * SM_BLOCK;
+                const unsigned long long kk = k < K ? cost_key(J[q], k) : ~0ull;
+                key = kk < key ? kk : key;
+            }
+        }
+    } else {
+        for (int k = tid; k < K; k += SM_BLOCK) {
+            const unsigned long long kk = cost_key(cost[k], k);
+            key = kk < key ? kk : key;
+        }
     }
     key = wave_min(key);
     if (lane == 0) kred[wv] = key;
@@ -117,51 +168,51 @@ __global__ __launch_bounds__(SM_BLOCK) void select_softmin(
     for (int q = 1; q < SM_BLOCK / 64; ++q) m = kred[q] < m ? kred[q] : m;
     if (blockIdx.x == 0 && tid == 0) publish_result(out, out_host, m, seq, 0);
     const bool any = m != ~0ull;
-    const float jmin = any ? key_cost(m) : 0.0f;
-    const int rows = 2 * N;
-    const int r0 = blockIdx.x * SM_ROWS;
-    float acc[SM_ROWS + 1];
+    if (any) jmin = key_cost(m);
+    float acc[ROWS + 1];
 #pragma unroll
-    for (int j = 0; j <= SM_ROWS; ++j) acc[j] = 0.0f;
+    for (int j = 0; j <= ROWS; ++j) acc[j] = 0.0f;
     if (any) {
-        // SM_UNROLL candidates per thread per pass, all loads issued before
-        // any is used; candidates still accumulate in the order k = tid,
-        // tid + SM_BLOCK, ... for every thread
-        for (int kb = tid; kb < K; kb += SM_BLOCK * SM_UNROLL) {
+        // candidates accumulate in the order k = tid, tid + SM_BLOCK, ... for
+        // every thread
+        for (int kb = tid; kb < K; kb += STRIDE) {
             float w[SM_UNROLL];
-            float u[SM_ROWS][SM_UNROLL];
-#pragma unroll
-            for (int q = 0; q < SM_UNROLL; ++q) {
-                const int k = kb + q * SM_BLOCK;
-                const float J = k < K ? cost[k] : __builtin_inff();
-#pragma unroll
-                for (int j = 0; j < SM_ROWS; ++j) {
-                    const int r = r0 + j;
-                    u[j][q] = (k < K && r < rows) ? controls[(size_t)r * K + k] : 0.0f;
+            if constexpr (ROWS < 4) {
+                if (kb != tid) {
+                    load_costs(kb);
+                    load_controls(kb);
                 }
-                w[q] = isfinite(J) ? __expf(-(J - jmin) * inv_lambda) : 0.0f;
+#pragma unroll
+                for (int q = 0; q < SM_UNROLL; ++q) w[q] = weight(J[q]);
+            } else {
+#pragma unroll
+                for (int q = 0; q < SM_UNROLL; ++q) {
+                    load_cost(kb, q);
+                    load_control(kb, q);
+                    w[q] = weight(J[q]);
+                }
             }
 #pragma unroll
             for (int q = 0; q < SM_UNROLL; ++q) {
-                acc[SM_ROWS] += w[q];
+                acc[ROWS] += w[q];
 #pragma unroll
-                for (int j = 0; j < SM_ROWS; ++j)
+                for (int j = 0; j < ROWS; ++j)
                     acc[j] += w[q] * clamp_ctrl(u[j][q], r0 + j, drate_max);
             }
         }
     }
 #pragma unroll
-    for (int j = 0; j <= SM_ROWS; ++j) {
+    for (int j = 0; j <= ROWS; ++j) {
         const float v = wave_sum(acc[j]);
         if (lane == 0) fred[wv][j] = v;
     }
     __syncthreads();
-    if (tid < SM_ROWS && r0 + tid < rows) {
-        float num = fred[0][tid], den = fred[0][SM_ROWS];
+    if (tid < ROWS && r0 + tid < rows) {
+        float num = fred[0][tid], den = fred[0][ROWS];
 #pragma unroll
         for (int q = 1; q < SM_BLOCK / 64; ++q) {
             num += fred[q][tid];
-            den += fred[q][SM_ROWS];
+            den += fred[q][ROWS];
         }
         plan[r0 + tid] = any ? num / den : 0.0f;
     }
@@ -187,9 +238,24 @@ hipError_t launch_select(int mode, float lambda, const float *controls, const fl
                            cost, K, controls, N, drate_max, 1, plan_out, part_keys,
                            counters + 0, out, out_host, seq, SampleArgs{});
     } else {
-        const unsigned groups = (unsigned)((2 * N + SM_ROWS - 1) / SM_ROWS);
-        hipLaunchKernelGGL(select_softmin, dim3(groups), dim3(SM_BLOCK), 0, s, cost, K,
-                           controls, N, drate_max, 1.0f / lambda, plan_out, out, out_host, seq);
+        // The fewest entries a workgroup that still leave no compute unit two
+        // workgroups, times with launch and wait: K = 10 007, N = 73 18.5 -> 15.6 us (one entry; two 16.5), 65 536
+        // x 50 45.9 -> 24.6, 65 536 x 200 51.9 -> 31.6 (two; one 37.7), 4 096 x
+        // 100 15.3 -> 13.6; beyond, every workgroup's own pass over the costs
+        // weighs more: 4 096 x 1 000 14.5 with four, 19.1 with two. Near the lines
+        // the forms differ by little: 16 384 x 200 18.4 with four, 18.3 with two.
+        const int rows = 2 * N;
+#define PLAN_LAUNCH(R)                                                                        \
+    hipLaunchKernelGGL(select_softmin<R>, dim3((unsigned)((rows + R - 1) / R)), dim3(SM_BLOCK), \
+                       0, s, cost, K, controls, N, drate_max, 1.0f / lambda, plan_out, out,   \
+                       out_host, seq)
+        if (rows <= SM_GROUPS)
+            PLAN_LAUNCH(1);
+        else if (rows <= 2 * SM_GROUPS)
+            PLAN_LAUNCH(2);
+        else
+            PLAN_LAUNCH(4);
+#undef PLAN_LAUNCH
     }
     return hipGetLastError();
 }

@@ -357,9 +357,14 @@ plan_status_t plan_create(plan_ctx **out, const plan_vehicle_t *veh, const plan_
         const long long most = ((long long)max_K + 63) / 64 / c->simds;
         const size_t workers =
             (size_t)(most < EST_MAX_ROUNDS ? most : EST_MAX_ROUNDS) * c->simds;
-        CREATE_TRY(hipMalloc(&c->est_handoff, (sizeof(float) * 512 + sizeof(int)) * workers));
-        c->est_flag = reinterpret_cast<int *>(c->est_handoff + 512 * workers);
-        CREATE_TRY(hipMemset(c->est_flag, 0, sizeof(int) * workers));
+        if (hipMalloc(&c->est_handoff, (sizeof(float) * 512 + sizeof(int)) * workers) ==
+            hipSuccess) {
+            c->est_flag = reinterpret_cast<int *>(c->est_handoff + 512 * workers);
+            CREATE_TRY(hipMemset(c->est_flag, 0, sizeof(int) * workers));
+        } else {
+            c->est_handoff = nullptr;  // launches then keep one group per wave
+            (void)hipGetLastError();
+        }
     }
     CREATE_TRY(plan::launch_order_reset(c->ow, c->stream));
     CREATE_TRY(hipEventCreate(&c->ev0));

@@ -978,11 +978,29 @@ static plan_status_t grad_check(plan_ctx *c, const char *fn, const float *state0
     return PLAN_OK;
 }
 
-// Checkpoint interval of the parallel backward pass in the workspace that
-// interval C sizes: that pass keeps recomputed states in LDS, so the part meant
-// for them holds checkpoints too. It wants short segments (they are recomputed
-// in parallel), but not under four steps, where the forward pass's stores cost
-// more than the recomputation. The gradient does not depend on it.
+// Whether a gradient takes the parallel backward pass: by K, N and S alone, so
+// that its bits do not depend on the caller's interval C. That pass keeps
+// recomputed states in LDS, up to ADJOINT_LINEAR_STEPS of a segment, and its
+// checkpoints need 13 (ceil(N / c) + 1) floats a candidate with c the longest
+// such segment. The workspace of every C holds them if the smallest one does:
+// 13 (N / C + 1) + 14 C S >= 13 + 2 sqrt(13 * 14 N S). That ends at about
+// 110 000 steps, or 4 S intervals where only one interval fits a segment.
+static bool linear_wanted(const plan_ctx *c, int K, int N, int S) {
+    const int longest = plan::ADJOINT_LINEAR_STEPS / S;
+    // Up to 24 candidates per compute unit (six rounds of workgroups of four)
+    // it is faster: N = 100, C = 10, with the forward pass, against the serial
+    // one: K = 16 80 against 237 us, 1 024 83 against 245, 4 096 213 against 265,
+    // 6 000 224 against 270; at 8 192 they are even (270), at 16 384 the serial
+    // one is 1.6 times as fast (its waves have SIMDs to themselves up to there).
+    if (longest < 1 || K > 6 * c->simds) return false;
+    const double ckpt = 13.0 * ((N - 1) / longest + 1);
+    return ckpt * ckpt <= 4.0 * 13.0 * 14.0 * (double)N * S;
+}
+
+// Its checkpoint interval in the workspace that interval C sizes. It wants
+// short segments (they are recomputed in parallel), but not under four steps,
+// where the forward pass's stores cost more than the recomputation. The
+// gradient does not depend on it.
 static int linear_interval(int N, int C, int S) {
     const long long room = 13ll * ((N + C - 1) / C + 1) + 14ll * C * S;
     long long c = S >= 4 ? 1 : (4 + S - 1) / S;
@@ -997,16 +1015,8 @@ static plan_status_t grad_launch(plan_ctx *c, const float *state0, const float *
                                  int K, int N, const float *weight_dev, int checkpoint_every,
                                  float *cost_dev, float *grad_dev, float *ws) {
     int C = checkpoint_every < N ? checkpoint_every : N;
-    // Up to 24 candidates per compute unit (six rounds of workgroups of four)
-    // the backward pass whose steps are linearised in parallel is faster: N =
-    // 100, C = 10, with the forward pass, against the serial one: K = 16 80
-    // against 237 us, 1 024 83 against 245, 4 096 213 against 265, 6 000 224
-    // against 270; at 8 192 they are even (270), at 16 384 the serial one is 1.6
-    // times as fast (its waves have SIMDs to themselves up to there).
-    const int fine = linear_interval(N, C, c->integ.substeps);
-    const bool linear = K <= 6 * c->simds &&
-                        (long long)fine * c->integ.substeps <= plan::ADJOINT_LINEAR_STEPS;
-    if (linear) C = fine;
+    const bool linear = linear_wanted(c, K, N, c->integ.substeps);
+    if (linear) C = linear_interval(N, C, c->integ.substeps);
     const int nseg = (N + C - 1) / C;
     float *ckpt = ws;
     float *seg = ckpt + (size_t)(nseg + 1) * 13 * (size_t)K;

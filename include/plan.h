@@ -238,10 +238,10 @@ plan_status_t plan_rollout_chunk(plan_ctx *ctx, float *state_dev, float *cost_de
  * The backward kernel splits each candidate's wheels over 1, 2 or 4 lanes
  * (the automatic choice of plan_rollout, or the lanes set by
  * plan_set_launch); the result is bit-identical for every choice. Up to 24
- * candidates per compute unit another backward kernel linearises the steps in
- * parallel; its gradients differ from the first one's by rounding only. Which
- * of the two runs depends on K, N and the substeps S alone (the second one's
- * horizons end at about 110 000 steps N S), so for given K, N and S the result
+ * candidates per compute unit and about 110 000 steps N S, where that is
+ * faster, another backward kernel linearises the steps in parallel; its
+ * gradients differ from the first one's by rounding only. Which of the two runs
+ * depends on K, N and the substeps S alone, so for given K, N and S the result
  * is bit-identical for every lane count and every checkpoint_every.
  * The forward pass is one launch that stores the checkpoints; the backward
  * pass is a second. The library grows an internal workspace of

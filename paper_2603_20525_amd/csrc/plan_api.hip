@@ -985,16 +985,26 @@ static plan_status_t grad_check(plan_ctx *c, const char *fn, const float *state0
 // such segment. The workspace of every C holds them if the smallest one does:
 // 13 (N / C + 1) + 14 C S >= 13 + 2 sqrt(13 * 14 N S). That ends at about
 // 110 000 steps, or 4 S intervals where only one interval fits a segment.
+//
+// In us, the serial pass takes 2 a step. The parallel one runs a round of
+// workgroups (one a compute unit, four candidates each) after the other, and a
+// round takes 4, 0.16 a step and 0.5 for each step that it recomputes in
+// series: per window of states the longest segment's, or the eight of two
+// passes of four. Over 275 sizes that picks the faster one, or one at most 5 %
+// slower. With the forward pass, parallel against serial: K = 16 to 1 024, N = 1
+// 14.7 / 15.4, 5 18.9 / 22.4, 100 83 / 245; 4 096 x 5 44.6 / 22.0, x 20 63.9 /
+// 60.5, x 100 213 / 265; 6 000 x 20 85.8 / 65.8, x 40 (four substeps of ten)
+// 112.6 / 112.1, x 100 224 / 270; 4 096 x 2 of 160 substeps 1 044 / 772. At
+// 8 192 x 100 they are even (270), at 16 384 the serial one is 1.6 times as fast
+// (its waves have SIMDs to themselves up to there).
 static bool linear_wanted(const plan_ctx *c, int K, int N, int S) {
     const int longest = plan::ADJOINT_LINEAR_STEPS / S;
-    // Up to 24 candidates per compute unit (six rounds of workgroups of four)
-    // it is faster: N = 100, C = 10, with the forward pass, against the serial
-    // one: K = 16 80 against 237 us, 1 024 83 against 245, 4 096 213 against 265,
-    // 6 000 224 against 270; at 8 192 they are even (270), at 16 384 the serial
-    // one is 1.6 times as fast (its waves have SIMDs to themselves up to there).
     if (longest < 1 || K > 6 * c->simds) return false;
     const double ckpt = 13.0 * ((N - 1) / longest + 1);
-    return ckpt * ckpt <= 4.0 * 13.0 * 14.0 * (double)N * S;
+    if (ckpt * ckpt > 4.0 * 13.0 * 14.0 * (double)N * S) return false;
+    const double steps = (double)N * S, rounds = (K - 1) / c->simds + 1;
+    const double windows = ((N - 1) / longest + 1);
+    return rounds * (4.0 + 0.16 * steps + 0.5 * windows * (S > 8 ? S : 8)) <= 2.0 * steps;
 }
 
 // Its checkpoint interval in the workspace that interval C sizes. It wants

@@ -49,3 +49,18 @@ def test_checkpoint_interval_changes_no_bit(N, S):
         Jc, gc = grad(pl, s0, u, C)
         assert torch.equal(Jc, J) and torch.equal(gc, g), C
     pl.close()
+
+
+# a few steps of many candidates, few but long segments
+@pytest.mark.parametrize("N,S", [(1, 1), (4, 1), (5, 1), (20, 1), (2, 160), (5, 100)])
+def test_sizes_the_parallel_pass_is_slow_at_take_the_serial_one(N, S):
+    """Their gradients are the bits of a launch of more candidates, which always
+    takes the serial pass."""
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    pl, s0, u = planner(24 * units + 8, N, S, 0.02)
+    want = grad(pl, s0, u, 10)
+    for K in (24 * units, 16 * units + 1):
+        J, g = grad(pl, s0, u[:, :, :K].contiguous(), 10)
+        assert torch.equal(J, want[0][:K]) and torch.equal(g, want[1][:, :, :K])
+    assert want[1].any()
+    pl.close()

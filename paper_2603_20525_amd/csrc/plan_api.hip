@@ -493,6 +493,17 @@ static plan_status_t order_candidates(plan_ctx *c, RolloutArgs &a, float delta0,
 static plan_status_t launch(plan_ctx *c, RolloutArgs &a, Kind kind) {
     int lanes, block;
     auto_launch(a.K, c->simds, &lanes, &block);
+    // Several Euler substeps an interval with given controls, no selection:
+    // two waves of two lanes do beat one of one lane, whose cells such a kernel
+    // does not request ahead. 65 000 candidates, two lanes against one: 2 substeps
+    // x 30 intervals 62.1 and 64.9 us, 5 x 20 100.7 and 107.3, 20 x 8 158.9 and
+    // 173.6; with a costmap 4 x 20 85.5 and 95.3. Not so in the chunked form (4 x
+    // 24 111.6 and 100.4), with selection (123.0 and 114.6) and drawn (4 x 20 87
+    // and 79).
+    if (kind == Kind::plain && lanes == 1 && a.K < 65536 && a.method == 0 && a.S > 1) {
+        lanes = 2;
+        block = 64;
+    }
     if (c->lanes_opt) lanes = c->lanes_opt;
     if (c->block_opt) block = c->block_opt;
     a.order = nullptr;

@@ -1,0 +1,43 @@
+"""Lanes that launches of several substeps an interval take between the sizes at
+which one lane gives every SIMD a wave and 65 536 candidates, and their results
+against one and two lanes set by hand."""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2603_20525_amd import inputs  # noqa: E402
+from paper_2603_20525_amd import plan as P  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("costmap", [False, True])
+@pytest.mark.parametrize("K,S,lanes", [(32768, 5, 2), (32769, 1, 1), (32769, 2, 2),
+                                       (32769, 3, 2), (40003, 5, 2), (65535, 4, 2),
+                                       (65536, 4, 1)])
+def test_given_controls(K, S, lanes, costmap):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    N = 3
+    w = inputs.c2(K=8, N=8)
+    T = w.terrain
+    g = torch.Generator(device="cuda")
+    g.manual_seed(K + S)
+    pl = P.Planner(w.vehicle, w.cost, dict(w.integ, substeps=S), K, N, T.W, T.H)
+    cm = torch.rand(T.H, T.W, generator=g, device="cuda") if costmap else None
+    pl.set_terrain(torch.from_numpy(T.height).cuda(), T.x0, T.y0, T.res, cm)
+    u = 0.3 * torch.randn(N, 2, K, generator=g, device="cuda")
+
+    def run():
+        J, fs = torch.full((K,), -7.0, device="cuda"), torch.full((13, K), -7.0, device="cuda")
+        pl.rollout(w.state0, u, J, fs)
+        return J, fs
+
+    J, fs = run()
+    assert pl.get_launch()[0] == lanes
+    assert torch.isfinite(J).any()
+    for hand in (1, 2):
+        pl.set_launch(hand, 0)
+        Jh, fh = run()
+        assert torch.equal(J, Jh) and torch.equal(fs, fh)
+    pl.close()

@@ -1,0 +1,38 @@
+// Rules by which launches are chosen from sizes alone: plain host code without
+// the HIP runtime, so that they can be tested without a device.
+#pragma once
+
+namespace plan {
+
+constexpr int EST_SHARE_MAX_ROUNDS = 6;
+
+// Waves per SIMD among which a rollout of the extended single-track model shares
+// its steps equally, or 0: it gives each wave a group of 64 candidates. Sharing
+// saves the last, partial round of waves but runs the rest with one wave per
+// SIMD fewer, which pays up to a remainder that depends on how well that many
+// waves hide each other's latency. 16 intervals of 50 substeps, shared / not, in
+// us: 66 000 candidates (1.01 waves per SIMD) 262 / 342, 80 000 (1.22) 307 / 340,
+// 90 000 (1.37) 370 / 343; 137 000 (2.09) 339 / 468, 170 000 (2.59) 416 / 473,
+// 185 000 (2.82) 501 / 499; 204 288 (3.12) 472 / 597, 240 000 (3.66) 552 / 598;
+// 270 000 (4.12) 592 / 725, 300 000 (4.58) 826 / 820; 350 000 (5.34) 739 / 851;
+// 400 000 (6.10) 827 / 981.
+// A single substep an interval streams its controls besides, which fewer waves
+// hide worse, so that only smaller remainders pay: 100 intervals, 66 000 46.7 /
+// 50.9, 80 000 55.4 / 51.0; 150 000 (2.29) 62.1 / 70.1, 170 000 78.0 / 73.4;
+// 204 288 87.4 / 91.4, 240 000 102.8 / 97.8; 270 000 117.9 / 123.7.
+// And the hand-off of a group takes some microseconds, so a few steps are not
+// shared: 66 000 x 10 11.6 / 9.4, x 20 15.1 / 13.3, x 30 18.5 / 18.3, x 50 26.1 /
+// 27.3; 400 000 x 5 16.6 / 11.5, x 20 34.8 / 33.1, x 30 46.7 / 46.1.
+inline int est_share_rounds(int groups, int simds, int N, int S) {
+    const int rounds = groups / simds, rest = groups - rounds * simds;
+    if (rounds < 1 || rounds > EST_SHARE_MAX_ROUNDS || rest == 0) return 0;
+    if ((long long)N * S < 25) return 0;
+    int eighths;  // of a round that may remain
+    if (S == 1)
+        eighths = rounds == 1 ? 1 : 2;
+    else
+        eighths = rounds == 1 ? 2 : rounds <= 3 ? 6 : 4;
+    return 8ll * rest <= (long long)eighths * simds ? rounds : 0;
+}
+
+}  // namespace plan

@@ -12,6 +12,7 @@
 #include <string>
 
 #include "../../include/plan.h"
+#include "launch_rules.h"
 #include "plan_internal.h"
 
 using plan::RolloutArgs;
@@ -73,7 +74,7 @@ struct plan_ctx {
 
 static thread_local std::string g_create_err;
 
-constexpr int EST_MAX_ROUNDS = 6;  // waves per SIMD
+constexpr int EST_MAX_ROUNDS = plan::EST_SHARE_MAX_ROUNDS;
 
 // Fixed adjoint workspace of plan_rollout_grad_noalloc, for callers that
 // cannot allocate device memory inside a call. One copy per GPU, held until
@@ -726,25 +727,15 @@ plan_status_t plan_select_sampled(plan_ctx *c, const plan_sample_t *spec, const 
     return want ? wait_result(c, seq, best_k, best_cost) : PLAN_OK;
 }
 
-// Waves per SIMD among which an EST launch shares its steps equally, or 0: it
-// gives each wave a group of 64 candidates. Sharing saves the last, partial
-// round of waves but runs the rest with one wave per SIMD fewer, which pays up
-// to a remainder that depends on how well that many waves hide each other's
-// latency. 800 steps, shared against not, in us: 66 000 candidates (1.01 waves
-// per SIMD) 274 / 345, 80 000 (1.22) 334 / 339, 90 000 (1.37) 370 / 343;
-// 137 000 (2.09) 373 / 485, 170 000 (2.59) 464 / 490, 185 000 (2.82) 501 / 499;
-// 204 288 (3.12) 521 / 616, 240 000 (3.66) 622 / 641; 270 000 (4.12) 726 / 821,
-// 300 000 (4.58) 826 / 820; 350 000 (5.34) 937 / 976; 400 000 (6.10) 1 054 /
-// 1 172. The shared form keeps state between the waves in the context, so it
-// stays on one stream and out of graphs, whose replays could overlap with other
-// launches. With a costmap the cells are the bound, not the last round.
-static int est_rounds(plan_ctx *c, int K) {
-    const int groups = (int)(((long long)K + 63) / 64), rounds = groups / c->simds;
-    const int rest = groups - rounds * c->simds;
-    if (!c->est_handoff || c->has_costmap || rounds < 1 || rounds > EST_MAX_ROUNDS || rest == 0)
-        return 0;
-    const int quarters = rounds == 1 ? 1 : rounds <= 3 ? 3 : 2;
-    if (4 * rest > quarters * c->simds) return 0;
+// Waves per SIMD among which an EST launch shares its steps, or 0. The shared
+// form keeps state between the waves in the context, so it stays on one stream
+// and out of graphs, whose replays could overlap with other launches. With a
+// costmap the cells are the bound, not the last round.
+static int est_rounds(plan_ctx *c, int K, int N) {
+    if (!c->est_handoff || c->has_costmap) return 0;
+    const int rounds =
+        plan::est_share_rounds((int)(((long long)K + 63) / 64), c->simds, N, c->integ.substeps);
+    if (rounds < 1 || rounds > EST_MAX_ROUNDS) return 0;
     if (c->est_stream_set && c->est_stream != c->stream) return 0;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(c->stream, &capture) != hipSuccess) {
@@ -787,7 +778,7 @@ plan_status_t plan_rollout_est(plan_ctx *c, const float state0[7], const float *
         const plan_status_t st = order_candidates(c, a, state0[5], state0[6]);
         if (st != PLAN_OK) return st;
     }
-    const int rounds = est_rounds(c, K);
+    const int rounds = est_rounds(c, K, N);
     if (rounds > 0)
         HIP_TRY(c, plan::launch_rollout_est_parts(a, rounds, c->simds, c->est_handoff,
                                                   c->est_flag, c->stream));

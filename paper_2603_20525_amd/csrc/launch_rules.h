@@ -35,4 +35,16 @@ inline int est_share_rounds(int groups, int simds, int N, int S) {
     return 8ll * rest <= (long long)eighths * simds ? rounds : 0;
 }
 
+// Whether the distance costmap of a W x H grid takes tiles of 16 x 16 nodes
+// instead of 32 x 32: where the larger ones number fewer than 7/4 per compute
+// unit, so that units would idle or wait for one that has two. Larger / smaller
+// tiles, in us: 256 x 256 nodes, 20 obstacles and a boundary 27.1 / 14.8, a
+// boundary of 1 300 edges 424 / 238; 600 x 600 (1.4 a unit) 23.7 / 16.0, 606 / 475;
+// 700 x 700 (1.9) 24.1 / 19.9, 612 / 620, with every perimeter in reach of every
+// node 118 / 131; 1 400 x 1 400 37.5 / 42.4, 1 306 / 1 485.
+inline bool costmap_small_tiles(int W, int H, int units) {
+    const long long tiles = (long long)((W + 31) / 32) * ((H + 31) / 32);
+    return 4 * tiles < 7ll * units;
+}
+
 }  // namespace plan

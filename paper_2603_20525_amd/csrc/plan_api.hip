@@ -921,7 +921,8 @@ plan_status_t plan_costmap_polygons(plan_ctx *c, const float *verts_dev, int V, 
     }
     HIP_TRY(c, hipSetDevice(c->device));
     HIP_TRY(c, plan::launch_costmap_polygons(verts_dev, ps, W, H, x0, y0, res, sigma, eps_dist,
-                                             accumulate != 0, costmap_dev, c->stream));
+                                             accumulate != 0, costmap_dev, c->simds / 4,
+                                             c->stream));
     return PLAN_OK;
 }
 

@@ -344,7 +344,7 @@ hipError_t launch_smooth(const float *h, int W, int H, const SmoothTaps &taps, f
 
 hipError_t launch_costmap_polygons(const float *verts, const PolygonSet &ps, int W, int H,
                                    float x0, float y0, float res, float sigma, float eps,
-                                   int accumulate, float *cm, hipStream_t s);
+                                   int accumulate, float *cm, int units, hipStream_t s);
 
 // Selection workspace sizes for a given maximum K / N.
 int select_blocks(int K);

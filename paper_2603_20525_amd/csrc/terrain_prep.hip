@@ -9,6 +9,7 @@
 //     features, interpolated at run time): at each node the sum over
 //     perimeters of sigma * max(0, 1 - sdist / eps)^2, sdist negative inside
 //     an obstacle and outside a path boundary, inside by the even-odd rule.
+#include "launch_rules.h"
 #include "plan_internal.h"
 
 namespace plan {
@@ -391,8 +392,8 @@ __device__ __forceinline__ float seg_dist2(float px, float py, float ax, float a
     return fmaf(qx, qx, qy * qy);
 }
 
-// A tile of CM_TILE x CM_TILE nodes per workgroup, CM_ROWS nodes of a column
-// per thread. Most tiles lie on the safe side of a perimeter (outside an
+// A tile of TILE x TILE nodes per workgroup, of a column's nodes every thread
+// takes as many as BLOCK threads leave it. Most tiles lie on the safe side of a perimeter (outside an
 // obstacle, inside a path boundary) by more than eps, where every node's term
 // is exactly zero, so the workgroup first decides which perimeters can touch
 // it and then evaluates those alone, node by node as before and in the order
@@ -400,10 +401,12 @@ __device__ __forceinline__ float seg_dist2(float px, float py, float ax, float a
 // every node against every edge (2048 x 2048 nodes, 244 edges: 950-990 us);
 // now the writes and, per tile, one pass over the edges (the same map: 23 us).
 // 32 x 32 nodes keep that pass (one edge per thread and a barrier) small
-// against the tile's work while the tile stays small against an obstacle.
-constexpr int CM_TILE = 32;
-constexpr int CM_BLOCK = 512;
-constexpr int CM_ROWS = CM_TILE * CM_TILE / CM_BLOCK;
+// against the tile's work while the tile stays small against an obstacle. Maps
+// of few such tiles (costmap_small_tiles) take 16 x 16, a node a thread: the
+// bound there is a thread's chain over the edges of the perimeters that touch
+// its tile, on as many compute units as there are tiles.
+constexpr int CM_TILE = 32, CM_BLOCK = 512;
+constexpr int CM_TILE_SMALL = 16, CM_BLOCK_SMALL = 256;
 
 // Whether the perimeter e's edge a-b can come within reach of the tile with
 // centre (cx, cy) and half diagonal rho: a lower bound of the distance of
@@ -424,18 +427,20 @@ __device__ __forceinline__ bool crosses(float px, float py, float2 v0, float2 v1
     return px < xc;
 }
 
-__global__ __launch_bounds__(CM_BLOCK) void costmap_polygons(const float2 *__restrict__ verts,
+template <int TILE, int BLOCK>
+__global__ __launch_bounds__(BLOCK) void costmap_polygons(const float2 *__restrict__ verts,
                                                         const PolygonSet ps, int W, int H,
                                                         float x0, float y0, float res,
                                                         float sigma, float eps, float inv_eps,
                                                         int accumulate,
                                                         float *__restrict__ cm) {
+    constexpr int ROWS = TILE * TILE / BLOCK;
     __shared__ int off[MAX_POLYGONS + 1];
     __shared__ unsigned gap[MAX_POLYGONS];     // smallest tile_gap over the perimeter's edges
     __shared__ unsigned parity[MAX_POLYGONS];  // crossings seen from the tile's centre
     __shared__ unsigned long long touched;
     const int tid = threadIdx.x;
-    const int i0 = blockIdx.x * CM_TILE, j0 = blockIdx.y * CM_TILE;
+    const int i0 = blockIdx.x * TILE, j0 = blockIdx.y * TILE;
     if (tid <= MAX_POLYGONS) off[tid] = ps.offsets[tid];
     if (tid < MAX_POLYGONS) {
         gap[tid] = 0x7f800000u;  // +inf
@@ -445,13 +450,13 @@ __global__ __launch_bounds__(CM_BLOCK) void costmap_polygons(const float2 *__res
     {
         // the tile as its centre and half diagonal, from its corner nodes
         const float xa = fmaf((float)i0, res, x0), ya = fmaf((float)j0, res, y0);
-        const float xb = fmaf((float)min(i0 + CM_TILE - 1, W - 1), res, x0);
-        const float yb = fmaf((float)min(j0 + CM_TILE - 1, H - 1), res, y0);
+        const float xb = fmaf((float)min(i0 + TILE - 1, W - 1), res, x0);
+        const float yb = fmaf((float)min(j0 + TILE - 1, H - 1), res, y0);
         const float cx = 0.5f * (xa + xb), cy = 0.5f * (ya + yb);
         const float hx = 0.5f * (xb - xa), hy = 0.5f * (yb - ya);
         const float rho = sqrtf(fmaf(hx, hx, hy * hy));
         const int V = ps.count > 0 ? off[ps.count] : 0;
-        for (int e = tid; e < V; e += CM_BLOCK) {
+        for (int e = tid; e < V; e += BLOCK) {
             int lo = 0, hi = ps.count - 1;  // the perimeter of vertex e
             while (lo < hi) {
                 const int mid = (lo + hi + 1) >> 1;
@@ -479,12 +484,13 @@ __global__ __launch_bounds__(CM_BLOCK) void costmap_polygons(const float2 *__res
         if (tid == 0) touched = m;
     }
     __syncthreads();
-    const int i = i0 + (tid & (CM_TILE - 1)), jt = j0 + tid / CM_TILE;
+    const int i = i0 + (tid & (TILE - 1)), jt = j0 + tid / TILE;
+    if (i >= W || jt >= H) return;  // nodes past the grid (the rows below are tested with them)
     const float px = fmaf((float)i, res, x0);
-    float py[CM_ROWS], c[CM_ROWS];
+    float py[ROWS], c[ROWS];
 #pragma unroll
-    for (int q = 0; q < CM_ROWS; ++q) {
-        py[q] = fmaf((float)(jt + q * (CM_BLOCK / CM_TILE)), res, y0);
+    for (int q = 0; q < ROWS; ++q) {
+        py[q] = fmaf((float)(jt + q * (BLOCK / TILE)), res, y0);
         c[q] = 0.0f;
     }
     unsigned long long todo = touched;
@@ -495,10 +501,10 @@ __global__ __launch_bounds__(CM_BLOCK) void costmap_polygons(const float2 *__res
         const int p = __builtin_ctzll(todo);
         todo &= todo - 1;
         const int a = ps.offsets[p], m = ps.offsets[p + 1] - a;
-        float dmin[CM_ROWS];
-        bool inside[CM_ROWS];
+        float dmin[ROWS];
+        bool inside[ROWS];
 #pragma unroll
-        for (int q = 0; q < CM_ROWS; ++q) {
+        for (int q = 0; q < ROWS; ++q) {
             dmin[q] = __builtin_inff();
             inside[q] = false;
         }
@@ -506,14 +512,14 @@ __global__ __launch_bounds__(CM_BLOCK) void costmap_polygons(const float2 *__res
         for (int e = 0; e < m; ++e) {
             const float2 v1 = verts[a + e];
 #pragma unroll
-            for (int q = 0; q < CM_ROWS; ++q) {
+            for (int q = 0; q < ROWS; ++q) {
                 dmin[q] = fminf(dmin[q], seg_dist2(px, py[q], v0.x, v0.y, v1.x, v1.y));
                 if (crosses(px, py[q], v0, v1)) inside[q] = !inside[q];
             }
             v0 = v1;
         }
 #pragma unroll
-        for (int q = 0; q < CM_ROWS; ++q) {
+        for (int q = 0; q < ROWS; ++q) {
             // obstacle: negative inside; path boundary: negative outside
             const float d = sqrtf(dmin[q]);
             const float sd = (inside[q] == (ps.kinds[p] == 0)) ? -d : d;
@@ -521,10 +527,9 @@ __global__ __launch_bounds__(CM_BLOCK) void costmap_polygons(const float2 *__res
             c[q] = fmaf(sigma * mm, mm, c[q]);
         }
     }
-    if (i >= W) return;
 #pragma unroll
-    for (int q = 0; q < CM_ROWS; ++q) {
-        const int j = jt + q * (CM_BLOCK / CM_TILE);
+    for (int q = 0; q < ROWS; ++q) {
+        const int j = jt + q * (BLOCK / TILE);
         if (j >= H) break;
         const size_t o = (size_t)j * W + i;
         cm[o] = accumulate ? cm[o] + c[q] : c[q];
@@ -558,10 +563,16 @@ hipError_t launch_smooth(const float *h, int W, int H, const SmoothTaps &taps, f
 
 hipError_t launch_costmap_polygons(const float *verts, const PolygonSet &ps, int W, int H,
                                    float x0, float y0, float res, float sigma, float eps,
-                                   int accumulate, float *cm, hipStream_t s) {
-    dim3 grid((W + CM_TILE - 1) / CM_TILE, (H + CM_TILE - 1) / CM_TILE);
-    hipLaunchKernelGGL(costmap_polygons, grid, dim3(CM_BLOCK), 0, s, (const float2 *)verts, ps, W, H,
-                       x0, y0, res, sigma, eps, 1.0f / eps, accumulate, cm);
+                                   int accumulate, float *cm, int units, hipStream_t s) {
+    auto launch = [&](auto kernel, int tile, int block) {
+        hipLaunchKernelGGL(kernel, dim3((W + tile - 1) / tile, (H + tile - 1) / tile), dim3(block),
+                           0, s, (const float2 *)verts, ps, W, H, x0, y0, res, sigma, eps,
+                           1.0f / eps, accumulate, cm);
+    };
+    if (costmap_small_tiles(W, H, units))
+        launch(costmap_polygons<CM_TILE_SMALL, CM_BLOCK_SMALL>, CM_TILE_SMALL, CM_BLOCK_SMALL);
+    else
+        launch(costmap_polygons<CM_TILE, CM_BLOCK>, CM_TILE, CM_BLOCK);
     return hipGetLastError();
 }
 

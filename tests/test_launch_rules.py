@@ -22,6 +22,8 @@ int main(int n, char **v) {
     for (int i = 2; i < n; ++i) sscanf(v[i], "%d", &a[i - 2]);
     if (!strcmp(v[1], "est_share_rounds"))
         printf("%d", plan::est_share_rounds(a[0], a[1], a[2], a[3]));
+    if (!strcmp(v[1], "costmap_small_tiles"))
+        printf("%d", plan::costmap_small_tiles(a[0], a[1], a[2]));
     return 0;
 }
 ''')
@@ -46,3 +48,10 @@ int main(int n, char **v) {
     (204288, 1, 25, 3), (400000, 4, 5, 0), (400000, 2, 2**30, 6)])
 def test_est_shares_its_steps_where_that_is_faster(rule, K, N, S, rounds):
     assert rule("est_share_rounds", (K + 63) // 64, SIMDS, N, S) == rounds
+
+
+@pytest.mark.parametrize("W,H,small", [
+    (2, 2, 1), (64, 64, 1), (600, 600, 1), (700, 700, 0), (2048, 2048, 0), (1537, 1025, 0),
+    (32 * 447, 1, 1), (32 * 447 + 1, 1, 0), (1, 32 * 448, 0), (67108863, 1, 0)])
+def test_costmap_tiles_by_the_size_of_the_map(rule, W, H, small):
+    assert rule("costmap_small_tiles", W, H, SIMDS // 4) == small

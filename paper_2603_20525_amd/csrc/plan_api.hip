@@ -529,9 +529,17 @@ static plan_status_t launch(plan_ctx *c, RolloutArgs &a, Kind kind) {
     // node's cells gain from the shared L1 (4 096 x 100 there: 59 against 66).
     // Runge-Kutta the same, and without a costmap at any number of waves (9 425
     // x 60: 104.6 against 107.9 us; with one 111 against 107).
+    // A selection in the launch pays for every workgroup's turn at its key, 2 us
+    // for 256 of them, which the steps have to earn back: 64 against 256 threads,
+    // 4 096 candidates x 20 24.3 / 23.1 us, x 40 32.8 / 32.9, x 100 58.4 / 62.4,
+    // 2 048 x 20 22.9 / 23.1; and with a costmap, where a wave per unit gains
+    // little, 4 096 x 100 59.4 / 58.4, 1 500 x 100 57.5 / 57.9.
+    const bool fused = kind == Kind::fused || kind == Kind::fused_sampled;
+    const bool few = 4 * waves <= c->simds &&
+                     (!fused || waves <= (a.has_costmap ? 1ll : 6ll) * a.N);
     if (!c->block_opt && lanes > 1 &&
-        ((plan::steps_ahead(a, one_wave) && 4 * waves <= c->simds) ||
-         (plan::stages_ahead(a, one_wave) && (4 * waves <= c->simds || !a.has_costmap))))
+        ((plan::steps_ahead(a, one_wave) && few) ||
+         (plan::stages_ahead(a, one_wave) && (few || !a.has_costmap))))
         block = 64;
     c->last_lanes = lanes;
     c->last_block = block;

@@ -519,7 +519,16 @@ static plan_status_t launch(plan_ctx *c, RolloutArgs &a, Kind kind) {
     // at most one wave per SIMD: the kernels built for a wave that has its
     // SIMD to itself
     const long long waves = ((long long)a.K * lanes + 63) / 64;
-    const bool one_wave = waves <= c->simds;
+    bool one_wave = waves <= c->simds;
+    const bool unit_each = 4 * waves <= c->simds;  // no more waves than compute units
+    // Runge-Kutta's stages request their cells ahead where that pays: with a wave
+    // per unit, at two lanes, and at four lanes over horizons that spread the
+    // candidates over more cells than the caches hold. Over short ones, and with
+    // several substeps, the cells are there anyway and the requests cost
+    // instructions. Against the plain kernel's 256 threads: 9 425 candidates x 31
+    // 58.8 / 57.6 us, 4 500 x 50 90.2 / 88.0, 8 000 x 20 of 3 substeps 105.0 / 99.8;
+    // 10 761 x 71 120.9 / 142.1, 8 000 x 113 198 / 207, 4 500 x 84 148 / 146.
+    if (a.method == 1 && lanes == 4 && !unit_each) one_wave = one_wave && a.S == 1 && a.n1 >= 64;
     // Where those kernels request the cells a step ahead over a lane group and
     // the launch has no more waves than the chip has compute units, a wave per
     // unit beats four sharing one: 4 096 candidates x 100 steps 62.6 -> 57.9
@@ -527,19 +536,19 @@ static plan_status_t launch(plan_ctx *c, RolloutArgs &a, Kind kind) {
     // anyway and the larger workgroup is dispatched and reduced cheaper
     // (10 007 x 73: 46 against 51 us), and the kernels that wait for each
     // node's cells gain from the shared L1 (4 096 x 100 there: 59 against 66).
-    // Runge-Kutta the same, and without a costmap at any number of waves (9 425
-    // x 60: 104.6 against 107.9 us; with one 111 against 107).
+    // Runge-Kutta the same, and without a costmap at four lanes at any number of
+    // waves (9 425 x 60: 104.6 against 107.9 us; with one 111 against 107; two
+    // lanes, 20 000 x 43 107.0 against 101.4).
     // A selection in the launch pays for every workgroup's turn at its key, 2 us
     // for 256 of them, which the steps have to earn back: 64 against 256 threads,
     // 4 096 candidates x 20 24.3 / 23.1 us, x 40 32.8 / 32.9, x 100 58.4 / 62.4,
     // 2 048 x 20 22.9 / 23.1; and with a costmap, where a wave per unit gains
     // little, 4 096 x 100 59.4 / 58.4, 1 500 x 100 57.5 / 57.9.
     const bool fused = kind == Kind::fused || kind == Kind::fused_sampled;
-    const bool few = 4 * waves <= c->simds &&
-                     (!fused || waves <= (a.has_costmap ? 1ll : 6ll) * a.N);
+    const bool few = unit_each && (!fused || waves <= (a.has_costmap ? 1ll : 6ll) * a.N);
     if (!c->block_opt && lanes > 1 &&
         ((plan::steps_ahead(a, one_wave) && few) ||
-         (plan::stages_ahead(a, one_wave) && (few || !a.has_costmap))))
+         (plan::stages_ahead(a, one_wave) && (few || (lanes == 4 && !a.has_costmap)))))
         block = 64;
     c->last_lanes = lanes;
     c->last_block = block;

@@ -57,11 +57,11 @@ struct plan_ctx {
     // terrain preparation: intermediate grid of the separable smoothing
     float *smooth_tmp = nullptr;
     // equal shares of the EST rollout (launch_rollout_est_parts): the waves'
-    // states and flags, used on one stream, the first that launches it
+    // states and flags, and the end of the last launch that used them
     float *est_handoff = nullptr;
     int *est_flag = nullptr;
-    hipStream_t est_stream = nullptr;
-    bool est_stream_set = false;
+    hipEvent_t est_done = nullptr;
+    bool est_used = false;
     // adjoint workspace (grown on demand): state, checkpoints, segment scratch
     float *gws = nullptr;
     size_t gws_floats = 0;
@@ -139,6 +139,8 @@ static void release(plan_ctx *c) {
     (void)hipFree(c->sel_dev);
     (void)hipFree(c->gws);
     (void)hipFree(c->smooth_tmp);
+    if (c->est_used) (void)hipEventSynchronize(c->est_done);
+    if (c->est_done) (void)hipEventDestroy(c->est_done);
     (void)hipFree(c->est_handoff);
     (void)hipFree(c->ow.lat);
     (void)hipFree(c->ctrl_lane);
@@ -362,6 +364,7 @@ plan_status_t plan_create(plan_ctx **out, const plan_vehicle_t *veh, const plan_
             hipSuccess) {
             c->est_flag = reinterpret_cast<int *>(c->est_handoff + 512 * workers);
             CREATE_TRY(hipMemset(c->est_flag, 0, sizeof(int) * workers));
+            CREATE_TRY(hipEventCreateWithFlags(&c->est_done, hipEventDisableTiming | hipEventDisableSystemFence));
         } else {
             c->est_handoff = nullptr;  // launches then keep one group per wave
             (void)hipGetLastError();
@@ -745,24 +748,20 @@ plan_status_t plan_select_sampled(plan_ctx *c, const plan_sample_t *spec, const 
 }
 
 // Waves per SIMD among which an EST launch shares its steps, or 0. The shared
-// form keeps state between the waves in the context, so it stays on one stream
-// and out of graphs, whose replays could overlap with other launches. With a
-// costmap the cells are the bound, not the last round.
+// form keeps state between the waves in the context, so it stays out of graphs,
+// whose replays could overlap with other launches. With a costmap the cells are
+// the bound, not the last round.
 static int est_rounds(plan_ctx *c, int K, int N) {
     if (!c->est_handoff || c->has_costmap) return 0;
     const int rounds =
         plan::est_share_rounds((int)(((long long)K + 63) / 64), c->simds, N, c->integ.substeps);
     if (rounds < 1 || rounds > EST_MAX_ROUNDS) return 0;
-    if (c->est_stream_set && c->est_stream != c->stream) return 0;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(c->stream, &capture) != hipSuccess) {
         (void)hipGetLastError();  // another stream's capture: not an error of this call
         return 0;
     }
-    if (capture != hipStreamCaptureStatusNone) return 0;
-    c->est_stream = c->stream;
-    c->est_stream_set = true;
-    return rounds;
+    return capture == hipStreamCaptureStatusNone ? rounds : 0;
 }
 
 plan_status_t plan_rollout_est(plan_ctx *c, const float state0[7], const float *controls_dev,
@@ -796,10 +795,18 @@ plan_status_t plan_rollout_est(plan_ctx *c, const float state0[7], const float *
         if (st != PLAN_OK) return st;
     }
     const int rounds = est_rounds(c, K, N);
-    if (rounds > 0)
+    if (rounds > 0) {
+        // one launch at a time on the hand-off, whatever stream the last one was
+        // on: a stream's handle does not tell (it may have been destroyed with
+        // that launch pending and its handle given to another). The event costs
+        // 1.2 us between launches, with a system-scope release 3; the hand-off's
+        // accesses are device-scope by themselves.
+        if (c->est_used) HIP_TRY(c, hipStreamWaitEvent(c->stream, c->est_done, 0));
         HIP_TRY(c, plan::launch_rollout_est_parts(a, rounds, c->simds, c->est_handoff,
                                                   c->est_flag, c->stream));
-    else
+        HIP_TRY(c, hipEventRecord(c->est_done, c->stream));
+        c->est_used = true;
+    } else
         HIP_TRY(c, plan::launch_rollout_est(a, block, ((long long)K + 63) / 64 <= c->simds,
                                             c->stream));
     if (c->timing) {

@@ -12,6 +12,7 @@
 // roll and pitch) and, when a costmap is set, the cost at the four wheels.
 // Arithmetic is fixed by the source (no contraction, explicit fmaf), as in
 // the SRB kernel.
+#include "handoff.h"
 #include "plan_internal.h"
 #include "rollout_step.h"
 
@@ -305,6 +306,33 @@ __global__ __launch_bounds__(BLOCK) void rollout_est(const RolloutArgs a) {
     est_finish(a, k, st, J);
 }
 
+// A hand-off flag in device memory, written by a wave's first lane and known to
+// all of them.
+struct WaveFlag {
+    int *p;
+    __device__ __forceinline__ int load() const {
+        return __builtin_amdgcn_readfirstlane(
+            __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    }
+    __device__ __forceinline__ void store(int v) const {
+        if ((threadIdx.x & 63) == 0)
+            __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // the first lane alone gets the value before (the others v)
+    __device__ __forceinline__ int exchange(int v) const {
+        if ((threadIdx.x & 63) == 0)
+            v = __hip_atomic_exchange(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return v;
+    }
+    __device__ __forceinline__ int compare_exchange(int expected, int v) const {
+        if ((threadIdx.x & 63) == 0)
+            __hip_atomic_compare_exchange_strong(p, &expected, v, __ATOMIC_RELAXED,
+                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return __builtin_amdgcn_readfirstlane(expected);
+    }
+    __device__ __forceinline__ void pause() const { __builtin_amdgcn_s_sleep(32); }
+};
+
 // A launch of a few waves per SIMD and a remainder lasts as long as the SIMDs
 // that take a wave more than the others (204 288 candidates: 120 of 1 024 SIMDs
 // take four, the others three). Here exactly `rounds` waves per SIMD, the
@@ -316,8 +344,7 @@ __global__ __launch_bounds__(BLOCK) void rollout_est(const RolloutArgs a) {
 // the worker before it handed on long since: it ran that piece first, and all
 // parts are as long. Were it not there in time (the workers of a launch need
 // not all be running, or have started), the worker runs the piece itself.
-// One flag a worker: 0 at rest, 1 its state is there, 2 nobody waits for it
-// any more; whoever comes last puts it back to 0.
+// One flag a worker, as in handoff.h.
 template <bool S1, bool FAST>
 __global__ __launch_bounds__(256) void rollout_est_parts(const RolloutArgs a, long long part,
                                                          float *handoff, int *flag) {
@@ -345,21 +372,8 @@ __global__ __launch_bounds__(256) void rollout_est_parts(const RolloutArgs a, lo
         float J = 0.0f;
         long long from = 0;
         if (is_tail) {
-            int seen = 0;
-            for (int spin = 0; spin < 1 << 14 && seen != 1; ++spin) {
-                seen = __builtin_amdgcn_readfirstlane(__hip_atomic_load(
-                    &flag[worker - 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-                if (seen != 1) __builtin_amdgcn_s_sleep(32);
-            }
-            if (seen != 1) {
-                int none = 0;
-                if (lane == 0)
-                    __hip_atomic_compare_exchange_strong(&flag[worker - 1], &none, 2,
-                                                         __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                         __HIP_MEMORY_SCOPE_AGENT);
-                seen = __builtin_amdgcn_readfirstlane(none);
-            }
-            if (seen == 1) {
+            const WaveFlag theirs{&flag[worker - 1]};
+            if (handoff_take(theirs, 1 << 14)) {
                 asm volatile("" ::: "memory");  // the state after the flag
                 float *h = handoff + (size_t)(worker - 1) * 512 + lane;
 #pragma unroll
@@ -368,9 +382,7 @@ __global__ __launch_bounds__(256) void rollout_est_parts(const RolloutArgs a, lo
                                               __HIP_MEMORY_SCOPE_AGENT);
                 J = __hip_atomic_load(h + 7 * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                if (lane == 0)
-                    __hip_atomic_store(&flag[worker - 1], 0, __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
+                handoff_release(theirs);
                 from = o_lo;
             }
         }
@@ -382,9 +394,7 @@ __global__ __launch_bounds__(256) void rollout_est_parts(const RolloutArgs a, lo
                 __hip_atomic_store(h + q * 64, st[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __hip_atomic_store(h + 7 * 64, J, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the flag after the state
-            if (lane == 0 && __hip_atomic_exchange(&flag[worker], 1, __ATOMIC_RELAXED,
-                                                   __HIP_MEMORY_SCOPE_AGENT) == 2)
-                __hip_atomic_store(&flag[worker], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            handoff_give(WaveFlag{&flag[worker]});
         } else if (g * 64 + lane < a.K) {
             est_finish(a, k, st, J);
         }

@@ -364,7 +364,8 @@ plan_status_t plan_create(plan_ctx **out, const plan_vehicle_t *veh, const plan_
             hipSuccess) {
             c->est_flag = reinterpret_cast<int *>(c->est_handoff + 512 * workers);
             CREATE_TRY(hipMemset(c->est_flag, 0, sizeof(int) * workers));
-            CREATE_TRY(hipEventCreateWithFlags(&c->est_done, hipEventDisableTiming | hipEventDisableSystemFence));
+            CREATE_TRY(hipEventCreateWithFlags(
+                &c->est_done, hipEventDisableTiming | hipEventDisableSystemFence));
         } else {
             c->est_handoff = nullptr;  // launches then keep one group per wave
             (void)hipGetLastError();

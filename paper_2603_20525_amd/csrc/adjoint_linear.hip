@@ -84,7 +84,7 @@ __device__ __forceinline__ float pull_back(float lam, float acc0, float acc1, co
         PLAN_ROW("1", "fmac", "10", "7") PLAN_ROW("0", "fmac", "11", "8")   //
         PLAN_ROW("2", "fmac", "12", "9") PLAN_ROW("1", "fmac", "13", "10")  //
         PLAN_ROW("0", "fmac", "14", "11")
-        : "+v"(acc0), "+v"(acc1), "=&v"(acc2)
+        : "+&v"(acc0), "+&v"(acc1), "=&v"(acc2)
         : "v"(lam), "v"(q0.x), "v"(q0.y), "v"(q0.z), "v"(q0.w), "v"(q1.x), "v"(q1.y), "v"(q1.z),
           "v"(q1.w), "v"(q2.x), "v"(q2.y), "v"(q2.z), "v"(pr.x), "v"(pr.y));
 #undef PLAN_ROW

@@ -31,10 +31,16 @@
 // torque, P' x dFz/dP - n x (R dFz/dn), resolved about the three rotation axes
 // (P' the arm in the world, n the terrain normal in the world).
 //
-// A candidate whose motion or adjoint leaves the range of any vehicle (its
+// A candidate whose motion or adjoint comes near the end of float's range (its
 // state has blown up numerically while its cost is still finite) is pulled back
-// once more, step by step, as adjoint.hip does, so that the products that
-// overflow are the same ones.
+// step by step, as adjoint.hip does, so that the products that overflow are the
+// same ones. That is a chain as long as the serial kernel's, so it must not start
+// after the rest: the final states tell such candidates beforehand, and the first
+// workgroups of the launch take them, 32 candidates' worth each, while the others
+// leave them out. What only shows on the way (the adjoint, or a state that the
+// goal froze behind) is pulled back again by its own workgroup at its end. 4 096
+// candidates x 100 steps on side slopes, where a few per cent blow up: 317 to 485
+// us with all of them pulled back at the end, 217 to 243 now, 322 serially.
 #include "adjoint_step.h"
 
 namespace plan {
@@ -42,8 +48,12 @@ namespace {
 
 constexpr int BATCH = 16;       // steps linearised at a time
 constexpr int WAVES = 5;        // four linearise, the last one pulls back
-constexpr float WILD_RATE = 1e8f;  // m/s or rad/s
-constexpr float WILD_ADJOINT = 1e18f;
+// No product of a step's linearisation overflows below these: up to rates of 1e28
+// the gradients of 1 300 blown-up candidates had the infinities and NaN of the
+// serial pass (and its values, but for rounding).
+constexpr float WILD_RATE = 1e18f;  // m/s or rad/s
+constexpr float WILD_ADJOINT = 1e28f;
+constexpr int FRONT = 32;  // candidates that a workgroup at the front looks at
 
 // A - 1 and the gradient of the running cost, by columns: the thirteen states,
 // dd, ax (column 15 is not used). Rows in quads (x, y, z, psi), (th, ph, vy,
@@ -58,7 +68,8 @@ struct Linear {
     Batch batch[2];
     float st[ADJOINT_LINEAR_STEPS][4][14];  // recomputed states and the executed flag
     float g[ADJOINT_LINEAR_STEPS][4][2];    // the steps' gradients by (dd, ax)
-    int redo[4];                            // candidates to pull back step by step
+    int early[4], late[4];  // blown up by the final state; seen on the way
+    int list[FRONT], listed;  // candidates to pull back step by step
 };
 
 struct Column {
@@ -310,11 +321,12 @@ __device__ __forceinline__ void linearise(const RolloutArgs &a, const Arm &r, co
 }
 
 // The arguments are those of adjoint_backward in adjoint.hip; a segment has at
-// most ADJOINT_LINEAR_STEPS steps.
+// most ADJOINT_LINEAR_STEPS steps. The first `front` workgroups take the blown-up
+// candidates, the others four candidates each.
 template <bool CM>
 __global__ __launch_bounds__(64 * WAVES, 1) void adjoint_linear(
     const RolloutArgs a, int C, const float *__restrict__ ckpt,
-    const float *__restrict__ weight, float *__restrict__ grad) {
+    const float *__restrict__ weight, float *__restrict__ grad, int front) {
     __shared__ Linear L;
     const int t = threadIdx.x, lane = t & 63;
     const bool pulls = t >= 64 * (WAVES - 1);
@@ -325,7 +337,8 @@ __global__ __launch_bounds__(64 * WAVES, 1) void adjoint_linear(
 
     // recompute and linearise: wheel t & 3 of candidate c
     const int wheel_i = t & 3, c = (t >> 2) & 3;
-    const int k0 = blockIdx.x * 4;
+    const bool at_front = (int)blockIdx.x < front;
+    const int k0 = at_front ? 0 : ((int)blockIdx.x - front) * 4;
     const size_t kc = (size_t)min(k0 + c, a.K - 1);
     const float *up = a.controls + kc;
     const Arm arms[1] = {arm(a, wheel_i)};
@@ -344,24 +357,17 @@ __global__ __launch_bounds__(64 * WAVES, 1) void adjoint_linear(
         lx = dist > 0.0f ? w * a.w_g * gdx / dist : 0.0f;
         ly = dist > 0.0f ? w * a.w_g * gdy / dist : 0.0f;
     };
-    {
-        float lx, ly;
-        terminal(kjc, wJ, lx, ly);
-        lam = j == 0 ? lx : j == 1 ? ly : 0.0f;
-    }
+    auto blown_up = [&](size_t k) {
+        const float *fs = ckpt + ((size_t)nseg * 13 + 6) * K + k;
+        float m = fabsf(fs[0]);
+#pragma unroll
+        for (int q = 1; q < 6; ++q) m = maxn(m, fabsf(fs[(size_t)q * K]));
+        return isfinite(a.cost[k]) && !(m < WILD_RATE);
+    };
 
-    // entries no step writes
-    for (int i = t; i < 2 * BATCH * 4 * 16; i += 64 * WAVES) {
-        Batch &B = L.batch[i / (BATCH * 4 * 16)];
-        const int o = i % (BATCH * 4 * 16);
-        float4 *cl = &B.col[0][0][0][0] + (o >> 4) * 48 + (o & 15);
-        (&B.pair[0][0][0])[o] = make_float2(0, 0);
-        cl[0] = cl[16] = cl[32] = make_float4(0, 0, 0, 0);
-    }
-    if (t < 4) L.redo[t] = 0;
-
-    // The states at which the steps of segments [lo, hi) start.
-    auto recompute = [&](int lo, int hi) {
+    // The states at which candidate kc's steps of segments [lo, hi) start.
+    auto recompute = [&](size_t kc, int lo, int hi) {
+        const float *up = a.controls + kc;
         const int n_lo = lo * C;
         for (int seg = lo + (t >> 4); seg < hi; seg += 4 * WAVES) {
             const int n0 = seg * C;
@@ -398,128 +404,161 @@ __global__ __launch_bounds__(64 * WAVES, 1) void adjoint_linear(
         }
     };
 
-    for (int hi = nseg; hi > 0; hi -= segs) {
-        const int lo = max(hi - segs, 0);  // segments [lo, hi)
-        const int n_lo = lo * C;
-        const int cnt = (min(N, hi * C) - n_lo) * S;  // their steps
-        const int batches = (cnt + BATCH - 1) / BATCH;
+    if (t == 0) L.listed = 0;
+    if (at_front) {
         __syncthreads();
-        recompute(lo, hi);
-        __syncthreads();
-        // step `slot` of a batch that starts at `first`; past the end the last
-        // one, as a step that was not taken
-        const int slot = (t >> 4) & (BATCH - 1);
-        auto fetch = [&](int first, StepIn &in) {
-            const int i = min(first + slot, cnt - 1);
-            const float *sl = &L.st[i][c][0];
-#pragma unroll
-            for (int q = 0; q < 13; ++q) in.st[q] = sl[q];
-            in.flag = first + slot < cnt ? sl[13] : 0.0f;
-            const size_t n = (size_t)(n_lo + i / S);
-            in.A = attitude(in.st[3], in.st[4], in.st[5]);
-            in.g = gather<CM>(a, in.A, grid_pos(a, in.st[0], in.st[1]), in.st[2], arms[0]);
-            in.u0 = up[(2 * n) * K];
-            in.u1 = up[(2 * n + 1) * K];
-        };
-        StepIn next;
-        if (!pulls) fetch((batches - 1) * BATCH, next);
-        for (int it = 0; it <= batches; ++it) {
-            if (!pulls) {
-                if (it < batches) {
-                    const int first = (batches - 1 - it) * BATCH;
-                    const StepIn in = next;
-                    fetch(max(first - BATCH, 0), next);
-                    __builtin_amdgcn_sched_barrier(0);
-                    Batch &B = L.batch[it & 1];
-                    linearise<CM>(a, arms[0], in, wheel_i == 0, B.col[slot][c], B.pair[slot][c]);
-                    float m = fabsf(in.st[6]);
-#pragma unroll
-                    for (int q = 7; q < 12; ++q) m = maxn(m, fabsf(in.st[q]));
-                    if (wheel_i == 0 && finite_c && !(m < WILD_RATE)) L.redo[c] = 1;
-                }
-            } else if (it > 0) {
-                const Batch &B = L.batch[(it - 1) & 1];
-                float e[BATCH];
-                // columns are read two steps ahead
-                Column r[BATCH];
-                auto read = [&](int b) {
-                    r[b] = Column{B.col[b][cj][0][j], B.col[b][cj][1][j], B.col[b][cj][2][j],
-                                  B.pair[b][cj][j]};
-                };
-                read(BATCH - 1);
-                read(BATCH - 2);
-#pragma unroll
-                for (int b = BATCH - 1; b >= 0; --b) {
-                    if (b > 1) read(b - 2);
-                    __builtin_amdgcn_sched_barrier(0);
-                    lam = pull_back(lam, j < 13 ? lam : 0.0f, wJ * r[b].q2.w, r[b]);
-                    e[b] = lam;
-                    peak = maxn(peak, fabsf(lam));
-                }
-                if (j == 13 || j == 14) {
-                    const int first = (batches - it) * BATCH;
-#pragma unroll
-                    for (int b = 0; b < BATCH; ++b) L.g[first + b][cj][j - 13] = e[b];
-                }
-            }
+        const int k = (int)blockIdx.x * FRONT + t;
+        if (t < FRONT && k < a.K && blown_up(k)) L.list[atomicAdd(&L.listed, 1)] = k;
+    } else {
+        {
+            float lx, ly;
+            terminal(kjc, wJ, lx, ly);
+            lam = j == 0 ? lx : j == 1 ? ly : 0.0f;
+        }
+        // entries no step writes
+        for (int i = t; i < 2 * BATCH * 4 * 16; i += 64 * WAVES) {
+            Batch &B = L.batch[i / (BATCH * 4 * 16)];
+            const int o = i % (BATCH * 4 * 16);
+            float4 *cl = &B.col[0][0][0][0] + (o >> 4) * 48 + (o & 15);
+            (&B.pair[0][0][0])[o] = make_float2(0, 0);
+            cl[0] = cl[16] = cl[32] = make_float4(0, 0, 0, 0);
+        }
+        if (t < 4) {
+            L.early[t] = blown_up((size_t)min(k0 + t, a.K - 1));
+            L.late[t] = 0;
+        }
+        for (int hi = nseg; hi > 0; hi -= segs) {
+            const int lo = max(hi - segs, 0);  // segments [lo, hi)
+            const int n_lo = lo * C;
+            const int cnt = (min(N, hi * C) - n_lo) * S;  // their steps
+            const int batches = (cnt + BATCH - 1) / BATCH;
             __syncthreads();
-        }
-        // the intervals' gradients, through the admissible-set clamps (identity
-        // branch inside)
-        for (int i = t; i < (cnt / S) * 8; i += 64 * WAVES) {
-            const int n = i >> 3, cg = (i >> 1) & 3, x = i & 1;
-            if (k0 + cg >= a.K) continue;
-            const size_t at = (2 * (size_t)(n_lo + n) + x) * K + k0 + cg;
-            const float u = a.controls[at], lim = x ? 1.0f : a.drate_max;
-            float gs = 0.0f;
-            for (int s = S - 1; s >= 0; --s) gs += L.g[n * S + s][cg][x];
-            const bool in = !(u < -lim) && !(u > lim) && isfinite(a.cost[k0 + cg]);
-            grad[at] = in ? (x ? a.accel_max * gs : gs) : 0.0f;
-        }
-    }
-    if (pulls && j < 15 && !(peak < WILD_ADJOINT) && isfinite(a.cost[kjc])) L.redo[cj] = 1;
-    __syncthreads();
-    if ((L.redo[0] | L.redo[1] | L.redo[2] | L.redo[3]) == 0) return;
-
-    // step by step (the first sixteen lanes), over the gradients stored above
-    __threadfence();
-    const float w = weight ? weight[kc] : 1.0f;
-    const bool redo = t < 16 && k0 + c < a.K && L.redo[c] != 0;
-    float lv[13];
+            recompute(kc, lo, hi);
+            __syncthreads();
+            // step `slot` of a batch that starts at `first`; past the end the last
+            // one, as a step that was not taken
+            const int slot = (t >> 4) & (BATCH - 1);
+            auto fetch = [&](int first, StepIn &in) {
+                const int i = min(first + slot, cnt - 1);
+                const float *sl = &L.st[i][c][0];
 #pragma unroll
-    for (int q = 0; q < 13; ++q) lv[q] = 0.0f;
-    terminal(kc, w, lv[0], lv[1]);
-    for (int hi = nseg; hi > 0; hi -= segs) {
-        const int lo = max(hi - segs, 0);
-        const int n_lo = lo * C;
-        __syncthreads();
-        recompute(lo, hi);
-        __syncthreads();
-        if (!redo) continue;
-        float gdd = 0.0f, gax = 0.0f;
-        for (int n = min(N, hi * C) - 1; n >= n_lo; --n) {
-            const float u0 = up[(2 * (size_t)n) * K], u1 = up[(2 * (size_t)n + 1) * K];
-            const float dd = clampf_nan(u0, -a.drate_max, a.drate_max);
-            const float ax = a.accel_max * clampf_nan(u1, -1.0f, 1.0f);
-            for (int s = S - 1; s >= 0; --s) {
-                const float *sl = &L.st[(n - n_lo) * S + s][c][0];
-                if (sl[13] != 0.0f) {
-                    float st[13], g1, g2;
+                for (int q = 0; q < 13; ++q) in.st[q] = sl[q];
+                in.flag = first + slot < cnt ? sl[13] : 0.0f;
+                const size_t n = (size_t)(n_lo + i / S);
+                in.A = attitude(in.st[3], in.st[4], in.st[5]);
+                in.g = gather<CM>(a, in.A, grid_pos(a, in.st[0], in.st[1]), in.st[2], arms[0]);
+                in.u0 = up[(2 * n) * K];
+                in.u1 = up[(2 * n + 1) * K];
+            };
+            StepIn next;
+            if (!pulls) fetch((batches - 1) * BATCH, next);
+            for (int it = 0; it <= batches; ++it) {
+                if (!pulls) {
+                    if (it < batches) {
+                        const int first = (batches - 1 - it) * BATCH;
+                        const StepIn in = next;
+                        fetch(max(first - BATCH, 0), next);
+                        __builtin_amdgcn_sched_barrier(0);
+                        Batch &B = L.batch[it & 1];
+                        linearise<CM>(a, arms[0], in, wheel_i == 0, B.col[slot][c], B.pair[slot][c]);
+                        float m = fabsf(in.st[6]);
 #pragma unroll
-                    for (int q = 0; q < 13; ++q) st[q] = sl[q];
-                    step_vjp<4>(a, arms, st, dd, ax, w, lv, &g1, &g2);
-                    gdd += g1;
-                    gax += g2;
+                        for (int q = 7; q < 12; ++q) m = maxn(m, fabsf(in.st[q]));
+                        if (wheel_i == 0 && finite_c && !(m < WILD_RATE)) L.late[c] = 1;
+                    }
+                } else if (it > 0) {
+                    const Batch &B = L.batch[(it - 1) & 1];
+                    float e[BATCH];
+                    // columns are read two steps ahead
+                    Column r[BATCH];
+                    auto read = [&](int b) {
+                        r[b] = Column{B.col[b][cj][0][j], B.col[b][cj][1][j], B.col[b][cj][2][j],
+                                      B.pair[b][cj][j]};
+                    };
+                    read(BATCH - 1);
+                    read(BATCH - 2);
+#pragma unroll
+                    for (int b = BATCH - 1; b >= 0; --b) {
+                        if (b > 1) read(b - 2);
+                        __builtin_amdgcn_sched_barrier(0);
+                        lam = pull_back(lam, j < 13 ? lam : 0.0f, wJ * r[b].q2.w, r[b]);
+                        e[b] = lam;
+                        peak = maxn(peak, fabsf(lam));
+                    }
+                    if (j == 13 || j == 14) {
+                        const int first = (batches - it) * BATCH;
+#pragma unroll
+                        for (int b = 0; b < BATCH; ++b) L.g[first + b][cj][j - 13] = e[b];
+                    }
                 }
+                __syncthreads();
             }
-            const bool in0 = !(u0 < -a.drate_max) && !(u0 > a.drate_max);
-            const bool in1 = !(u1 < -1.0f) && !(u1 > 1.0f);
-            if (wheel_i == 0) {
-                grad[(2 * (size_t)n) * K + kc] = in0 ? gdd : 0.0f;
-                grad[(2 * (size_t)n + 1) * K + kc] = in1 ? a.accel_max * gax : 0.0f;
+            // the intervals' gradients, through the admissible-set clamps (identity
+            // branch inside)
+            for (int i = t; i < (cnt / S) * 8; i += 64 * WAVES) {
+                const int n = i >> 3, cg = (i >> 1) & 3, x = i & 1;
+                if (k0 + cg >= a.K || L.early[cg]) continue;  // the front's
+                const size_t at = (2 * (size_t)(n_lo + n) + x) * K + k0 + cg;
+                const float u = a.controls[at], lim = x ? 1.0f : a.drate_max;
+                float gs = 0.0f;
+                for (int s = S - 1; s >= 0; --s) gs += L.g[n * S + s][cg][x];
+                const bool in = !(u < -lim) && !(u > lim) && isfinite(a.cost[k0 + cg]);
+                grad[at] = in ? (x ? a.accel_max * gs : gs) : 0.0f;
             }
-            gdd = 0.0f;
-            gax = 0.0f;
+        }
+        if (pulls && j < 15 && !(peak < WILD_ADJOINT) && isfinite(a.cost[kjc])) L.late[cj] = 1;
+        __syncthreads();
+        if (t < 4 && k0 + t < a.K && L.late[t] && !L.early[t])
+            L.list[atomicAdd(&L.listed, 1)] = k0 + t;
+    }
+    __syncthreads();
+
+    // step by step, four candidates at a time (the first sixteen lanes)
+    const int listed = L.listed;
+    // the gradients stored above are stored over (a fence in every workgroup
+    // would cost 0.1 us each: they write back the same L2s)
+    if (listed > 0) __threadfence();
+    for (int from = 0; from < listed; from += 4) {
+        const size_t kr = (size_t)L.list[min(from + c, listed - 1)];
+        const float *ur = a.controls + kr;
+        const float w = weight ? weight[kr] : 1.0f;
+        const bool redo = t < 16 && from + c < listed;
+        float lv[13];
+#pragma unroll
+        for (int q = 0; q < 13; ++q) lv[q] = 0.0f;
+        terminal(kr, w, lv[0], lv[1]);
+        for (int hi = nseg; hi > 0; hi -= segs) {
+            const int lo = max(hi - segs, 0);
+            const int n_lo = lo * C;
+            __syncthreads();
+            recompute(kr, lo, hi);
+            __syncthreads();
+            if (!redo) continue;
+            float gdd = 0.0f, gax = 0.0f;
+            for (int n = min(N, hi * C) - 1; n >= n_lo; --n) {
+                const float u0 = ur[(2 * (size_t)n) * K], u1 = ur[(2 * (size_t)n + 1) * K];
+                const float dd = clampf_nan(u0, -a.drate_max, a.drate_max);
+                const float ax = a.accel_max * clampf_nan(u1, -1.0f, 1.0f);
+                for (int s = S - 1; s >= 0; --s) {
+                    const float *sl = &L.st[(n - n_lo) * S + s][c][0];
+                    if (sl[13] != 0.0f) {
+                        float st[13], g1, g2;
+#pragma unroll
+                        for (int q = 0; q < 13; ++q) st[q] = sl[q];
+                        step_vjp<4>(a, arms, st, dd, ax, w, lv, &g1, &g2);
+                        gdd += g1;
+                        gax += g2;
+                    }
+                }
+                const bool in0 = !(u0 < -a.drate_max) && !(u0 > a.drate_max);
+                const bool in1 = !(u1 < -1.0f) && !(u1 > 1.0f);
+                if (wheel_i == 0) {
+                    grad[(2 * (size_t)n) * K + kr] = in0 ? gdd : 0.0f;
+                    grad[(2 * (size_t)n + 1) * K + kr] = in1 ? a.accel_max * gax : 0.0f;
+                }
+                gdd = 0.0f;
+                gax = 0.0f;
+            }
         }
     }
 }
@@ -529,13 +568,14 @@ __global__ __launch_bounds__(64 * WAVES, 1) void adjoint_linear(
 hipError_t launch_adjoint_linear(const RolloutArgs &a, int C, const float *ckpt,
                                  const float *weight, float *grad, hipStream_t s) {
     if ((long long)C * a.S > ADJOINT_LINEAR_STEPS) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)((a.K + 3) / 4));
+    const int front = (a.K + FRONT - 1) / FRONT;
+    const dim3 grid((unsigned)((a.K + 3) / 4 + front));
     if (a.has_costmap)
         hipLaunchKernelGGL(adjoint_linear<true>, grid, dim3(64 * WAVES), 0, s, a, C, ckpt, weight,
-                           grad);
+                           grad, front);
     else
         hipLaunchKernelGGL(adjoint_linear<false>, grid, dim3(64 * WAVES), 0, s, a, C, ckpt,
-                           weight, grad);
+                           weight, grad, front);
     return hipGetLastError();
 }
 

@@ -525,7 +525,7 @@ class Result(C.Structure):
 
 
 # The two structs' layouts for one packing call instead of a ctypes store per
-# field (submission 3.0 -> 2.4 us, result 1.0 -> 0.7)
+# field (submission 3.0 -> 2.4 us, result 1.0 -> 0.8)
 _REQUEST = struct.Struct("@Pii3fP13fPii10ffiffiPP")
 _RESULT = struct.Struct("@iifi3d")
 _RESULT_NAMES = tuple(n for n, _ in Result._fields_)
@@ -579,8 +579,8 @@ class Server:
     def __init__(self, vehicle, max_slots, max_K, max_N, max_W, max_H, budget_bytes,
                  chunk_intervals=16, stream=None):
         import torch
-        self._req, self._rid, self._res = Request(), C.c_int(-1), Result()
-        self._refs = C.byref(self._req), C.byref(self._rid), C.byref(self._res)
+        self._req, self._rid = Request(), C.c_int(-1)
+        self._refs = C.byref(self._req), C.byref(self._rid)
         self._params = {}
         self._cbuf = {}
         self._cn, self._sa, self._sq = C.c_int(0), C.c_int(0), C.c_int(0)
@@ -621,7 +621,7 @@ class Server:
             r.controls_dev, r.K, r.N = ptrs[2], K, N
             r.cost, r.integ = Cost(*c), Integ(*i)
             r.plan_dev, r.cost_dev = ptrs[3], ptrs[4]
-        req, rid, _ = self._refs
+        req, rid = self._refs
         st = self._calls[0](self.h, req, rid)
         if st != PLAN_OK:
             _scheck("plan_server_submit", st, self.h)
@@ -661,10 +661,11 @@ class Server:
         _scheck("plan_server_drain", _bind_server().plan_server_drain(self.h), self.h)
 
     def result(self, rid) -> dict:
-        st = self._calls[1](self.h, int(rid), self._refs[2])
+        r = Result()  # its own for each call: threads may read results at once
+        st = self._calls[1](self.h, int(rid), C.byref(r))
         if st != PLAN_OK:
             _scheck("plan_server_result", st, self.h)
-        out = dict(zip(_RESULT_NAMES, _RESULT.unpack_from(self._res)))
+        out = dict(zip(_RESULT_NAMES, _RESULT.unpack_from(r)))
         if out["status"] != 0:
             self._keep.pop(rid, None)
         return out

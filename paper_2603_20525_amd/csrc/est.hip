@@ -345,7 +345,7 @@ struct WaveFlag {
 // parts are as long. Were it not there in time (the workers of a launch need
 // not all be running, or have started), the worker runs the piece itself.
 // One flag a worker, as in handoff.h.
-template <bool S1, bool FAST>
+template <bool S1>
 __global__ __launch_bounds__(256) void rollout_est_parts(const RolloutArgs a, long long part,
                                                          float *handoff, int *flag) {
     const int worker =
@@ -386,7 +386,7 @@ __global__ __launch_bounds__(256) void rollout_est_parts(const RolloutArgs a, lo
                 from = o_lo;
             }
         }
-        est_steps<S1, true, false, FAST>(a, up, st, J, from, is_head ? o_hi : T);
+        est_steps<S1, true, false, true>(a, up, st, J, from, is_head ? o_hi : T);
         if (is_head) {
             float *h = handoff + (size_t)worker * 512 + lane;
 #pragma unroll
@@ -413,10 +413,13 @@ hipError_t launch_rollout_est(const RolloutArgs &a, int block, bool one_wave, hi
         return hipGetLastError();                                                            \
     }
 #define PLAN_LAUNCHES(B, ONE)                        \
-    PLAN_LAUNCH(B, ONE, true, true, false, false)    \
-    PLAN_LAUNCH(B, ONE, true, true, true, false)     \
     PLAN_LAUNCH(B, ONE, false, true, false, true)    \
     PLAN_LAUNCH(B, ONE, false, false, true, false)
+    // launches of up to one wave per SIMD take 64 threads
+    PLAN_LAUNCH(64, false, true, true, false, false)
+    PLAN_LAUNCH(64, false, true, true, true, false)
+    PLAN_LAUNCH(64, true, true, true, false, false)
+    PLAN_LAUNCH(64, true, true, true, true, false)
     PLAN_LAUNCHES(64, false)
     PLAN_LAUNCHES(64, true)
     PLAN_LAUNCHES(256, false)
@@ -436,10 +439,10 @@ hipError_t launch_rollout_est_parts(const RolloutArgs &a, int rounds, int simds,
     const unsigned lds = 160 * 1024 / (rounds + 1) + 1024;
     const dim3 grid((unsigned)(workers / 4));
     if (a.S == 1)
-        hipLaunchKernelGGL((rollout_est_parts<true, true>), grid, dim3(256), lds, s, a, part,
+        hipLaunchKernelGGL((rollout_est_parts<true>), grid, dim3(256), lds, s, a, part,
                            handoff, flag);
     else
-        hipLaunchKernelGGL((rollout_est_parts<false, true>), grid, dim3(256), lds, s, a, part,
+        hipLaunchKernelGGL((rollout_est_parts<false>), grid, dim3(256), lds, s, a, part,
                            handoff, flag);
     return hipGetLastError();
 }

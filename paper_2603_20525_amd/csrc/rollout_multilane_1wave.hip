@@ -93,11 +93,22 @@ hipError_t launch_ckpt_multi_1wave(const RolloutArgs &a, int lanes, int block, h
     return hipErrorInvalidValue;
 }
 
+// A tick of so few waves takes workgroups of 64.
 hipError_t launch_slots_multi_1wave(const RolloutArgs *slots, const TickTable &t, int *bad,
                                     SelectOut *ring, uint32_t seq, int lanes, int block,
                                     hipStream_t s) {
-    if (lanes == 2) return launch_slots_lanes<2>(slots, t, bad, ring, seq, true, block, s);
-    if (lanes == 4) return launch_slots_lanes<4>(slots, t, bad, ring, seq, true, block, s);
+    const unsigned grid = (unsigned)t.total_blocks;
+#define PLAN_LAUNCH(L, CMAP)                                                                  \
+    if (lanes == L && block == 64 && (t.costmap != 0) == CMAP) {                              \
+        hipLaunchKernelGGL((rollout_slots<L, 64, true, CMAP>), dim3(grid), dim3(64), 0, s,    \
+                           slots, t, bad, ring, seq);                                         \
+        return hipGetLastError();                                                             \
+    }
+    PLAN_LAUNCH(2, false)
+    PLAN_LAUNCH(2, true)
+    PLAN_LAUNCH(4, false)
+    PLAN_LAUNCH(4, true)
+#undef PLAN_LAUNCH
     return hipErrorInvalidValue;
 }
 

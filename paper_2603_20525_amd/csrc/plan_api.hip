@@ -533,6 +533,16 @@ static plan_status_t launch(plan_ctx *c, RolloutArgs &a, Kind kind) {
     // 58.8 / 57.6 us, 4 500 x 50 90.2 / 88.0, 8 000 x 20 of 3 substeps 105.0 / 99.8;
     // 10 761 x 71 120.9 / 142.1, 8 000 x 113 198 / 207, 4 500 x 84 148 / 146.
     if (a.method == 1 && lanes == 4 && !unit_each) one_wave = one_wave && a.S == 1 && a.n1 >= 64;
+    // Euler with given controls the same at four lanes without a costmap: up to
+    // 2.8 MB of them come from the caches without being asked for a trip ahead,
+    // and the launch that asks lasts longer. 6 000 candidates x 20 13.1 against
+    // 12.4 us, x 36 21.0 / 19.6 (with the selection 31.7 / 30.6), x 50 25.9 / 26.4,
+    // x 100 46.3 / 54.4; 4 200 x 70 33.7 / 36.1; 16 384 x 20 13.3 / 12.6, x 36 19.4 /
+    // 20.5. With a costmap (6 000 x 20 12.4 / 12.8), at two lanes (17 000 x 20 15.5 /
+    // 15.8) and with drawn controls (6 000 x 20 16.1 / 22.1) it never does.
+    if (plan::steps_ahead(a, one_wave) && lanes == 4 && !unit_each && !a.has_costmap &&
+        !sampled && (long long)a.K * (a.n1 - a.n0) < 350000)
+        one_wave = false;
     // Where those kernels request the cells a step ahead over a lane group and
     // the launch has no more waves than the chip has compute units, a wave per
     // unit beats four sharing one: 4 096 candidates x 100 steps 62.6 -> 57.9

@@ -47,4 +47,21 @@ inline bool costmap_small_tiles(int W, int H, int units) {
     return 4 * tiles < 7ll * units;
 }
 
+// Plan entries (of the 2 N) that a workgroup of the softmin takes: the fewest
+// that leave no unit of the chip's 256 two workgroups, times with launch and
+// wait: K = 10 007, N = 73 18.5 -> 15.6 us (one; two 16.5), 65 536 x 50 45.9 ->
+// 24.6, 65 536 x 200 51.9 -> 31.6 (two; one 37.7), 4 096 x 100 15.3 -> 13.6;
+// beyond, every workgroup's own pass over the costs weighs more: 4 096 x 1 000
+// 14.5 with four, 19.1 with two. Where one pass of 8 192 candidates is about
+// full, or a second one short, four take as long as two on half the workgroups:
+// four / two, 8 192 x 256 15.7 / 16.4, 12 363 x 228 15.6 / 17.7, 16 384 x 176 16.9
+// / 18.3; but 4 096 x 256 15.7 / 14.0, 12 363 x 150 18.5 / 17.1, 20 000 x 256 18.5 /
+// 17.3.
+inline int softmin_entries(int K, int N) {
+    const long long rows = 2ll * N;
+    if (rows <= 256) return 1;
+    const bool full_pass = K > 6144 && K < 20000 && !(rows <= 340 && K < 14336);
+    return rows <= 512 && !full_pass ? 2 : 4;
+}
+
 }  // namespace plan

@@ -8,6 +8,7 @@
 // sums per fixed chunk and then over chunks in index order. Multi-block
 // reductions finish in the last block to arrive (an atomic ticket), which
 // resets the ticket for the next call, so no memset is needed between calls.
+#include "launch_rules.h"
 #include "plan_internal.h"
 #include "select_common.h"
 
@@ -18,7 +19,6 @@ constexpr int SEL_BLOCK = 256;
 constexpr int SEL_ITEMS = 16;                      // candidates per thread
 constexpr int SEL_CHUNK = SEL_BLOCK * SEL_ITEMS;   // candidates per block
 constexpr int SM_UNROLL = 8;                       // softmin: candidates in flight per thread
-constexpr int SM_GROUPS = 256;                     // softmin: compute units of the chip
 constexpr int SM_BLOCK = 1024;                     // softmin: threads per block
 
 // --------------------------------------------------------------- terrain ----
@@ -238,20 +238,15 @@ hipError_t launch_select(int mode, float lambda, const float *controls, const fl
                            cost, K, controls, N, drate_max, 1, plan_out, part_keys,
                            counters + 0, out, out_host, seq, SampleArgs{});
     } else {
-        // The fewest entries a workgroup that still leave no compute unit two
-        // workgroups, times with launch and wait: K = 10 007, N = 73 18.5 -> 15.6 us (one entry; two 16.5), 65 536
-        // x 50 45.9 -> 24.6, 65 536 x 200 51.9 -> 31.6 (two; one 37.7), 4 096 x
-        // 100 15.3 -> 13.6; beyond, every workgroup's own pass over the costs
-        // weighs more: 4 096 x 1 000 14.5 with four, 19.1 with two. Near the lines
-        // the forms differ by little: 16 384 x 200 18.4 with four, 18.3 with two.
         const int rows = 2 * N;
 #define PLAN_LAUNCH(R)                                                                        \
     hipLaunchKernelGGL(select_softmin<R>, dim3((unsigned)((rows + R - 1) / R)), dim3(SM_BLOCK), \
                        0, s, cost, K, controls, N, drate_max, 1.0f / lambda, plan_out, out,   \
                        out_host, seq)
-        if (rows <= SM_GROUPS)
+        const int entries = softmin_entries(K, N);
+        if (entries == 1)
             PLAN_LAUNCH(1);
-        else if (rows <= 2 * SM_GROUPS)
+        else if (entries == 2)
             PLAN_LAUNCH(2);
         else
             PLAN_LAUNCH(4);

@@ -24,6 +24,8 @@ int main(int n, char **v) {
         printf("%d", plan::est_share_rounds(a[0], a[1], a[2], a[3]));
     if (!strcmp(v[1], "costmap_small_tiles"))
         printf("%d", plan::costmap_small_tiles(a[0], a[1], a[2]));
+    if (!strcmp(v[1], "softmin_entries"))
+        printf("%d", plan::softmin_entries(a[0], a[1]));
     return 0;
 }
 ''')
@@ -55,3 +57,11 @@ def test_est_shares_its_steps_where_that_is_faster(rule, K, N, S, rounds):
     (32 * 447, 1, 1), (32 * 447 + 1, 1, 0), (1, 32 * 448, 0), (67108863, 1, 0)])
 def test_costmap_tiles_by_the_size_of_the_map(rule, W, H, small):
     assert rule("costmap_small_tiles", W, H, SIMDS // 4) == small
+
+
+@pytest.mark.parametrize("K,N,entries", [
+    (1, 1, 1), (200000, 128, 1), (1, 129, 2), (4096, 256, 2), (6144, 256, 2), (6145, 256, 4),
+    (8192, 170, 2), (8192, 171, 4), (14335, 170, 2), (14336, 170, 4), (19999, 256, 4),
+    (20000, 256, 2), (20000, 257, 4), (1, 2**30, 4)])
+def test_softmin_entries_a_workgroup(rule, K, N, entries):
+    assert rule("softmin_entries", K, N) == entries

@@ -1084,6 +1084,14 @@ static plan_status_t grad_launch(plan_ctx *c, const float *state0, const float *
     // forward pass in one launch, storing the state at every C-th interval
     int lanes, block;
     auto_launch(K, c->simds, &lanes, &block);
+    // Several substeps keep two lanes below 65 536 candidates. 50 000 candidates,
+    // two lanes against one: 20 intervals of 4 441 and 455 us, 12 of 10 693 and 722,
+    // 15 of 30, whose segments no cache holds, 4 367 and 5 812; but 60 of 1 338 and
+    // 330, 30 of 2 333 and 331.
+    if (lanes == 1 && K < 65536 && a.S > 2) {
+        lanes = 2;
+        block = 64;
+    }
     if (c->lanes_opt) lanes = c->lanes_opt;
     if (c->block_opt) block = c->block_opt;
     const long long waves = ((long long)K * lanes + 63) / 64;

@@ -41,3 +41,31 @@ def test_given_controls(K, S, lanes, costmap):
         Jh, fh = run()
         assert torch.equal(J, Jh) and torch.equal(fs, fh)
     pl.close()
+
+
+@pytest.mark.parametrize("K,S,lanes", [(32769, 1, 1), (32769, 2, 1), (32769, 3, 2), (65535, 8, 2),
+                                       (65536, 8, 1)])
+def test_gradient(K, S, lanes):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    N = 4
+    w = inputs.c2(K=8, N=8)
+    T = w.terrain
+    g = torch.Generator(device="cuda")
+    g.manual_seed(K + S)
+    pl = P.Planner(w.vehicle, w.cost, dict(w.integ, substeps=S), K, N, T.W, T.H)
+    pl.set_terrain(torch.from_numpy(T.height).cuda(), T.x0, T.y0, T.res)
+    u = 0.3 * torch.randn(N, 2, K, generator=g, device="cuda")
+
+    def run():
+        J, gr = torch.full((K,), -7.0, device="cuda"), torch.full((N, 2, K), -7.0, device="cuda")
+        pl.rollout_grad(w.state0, u, J, gr, None, 3)
+        return J, gr
+
+    J, gr = run()
+    assert pl.get_launch()[0] == lanes and gr.any()
+    for hand in (1, 2):
+        pl.set_launch(hand, 0)
+        Jh, gh = run()
+        assert torch.equal(J, Jh) and torch.equal(gr, gh)
+    pl.close()

@@ -498,14 +498,23 @@ static plan_status_t order_candidates(plan_ctx *c, RolloutArgs &a, float delta0,
 static plan_status_t launch(plan_ctx *c, RolloutArgs &a, Kind kind) {
     int lanes, block;
     auto_launch(a.K, c->simds, &lanes, &block);
-    // Several Euler substeps an interval with given controls, no selection:
-    // two waves of two lanes do beat one of one lane, whose cells such a kernel
-    // does not request ahead. 65 000 candidates, two lanes against one: 2 substeps
-    // x 30 intervals 62.1 and 64.9 us, 5 x 20 100.7 and 107.3, 20 x 8 158.9 and
-    // 173.6; with a costmap 4 x 20 85.5 and 95.3. Not so in the chunked form (4 x
-    // 24 111.6 and 100.4), with selection (123.0 and 114.6) and drawn (4 x 20 87
-    // and 79).
-    if (kind == Kind::plain && lanes == 1 && a.K < 65536 && a.method == 0 && a.S > 1) {
+    // Several Euler substeps an interval keep two lanes where one lane's
+    // workgroups of 256 threads leave more than an eighth of the compute units
+    // without one: 10 substeps x 12 intervals with a costmap, two lanes against
+    // one, 33 000 candidates with selection 144 / 165 us, in chunks 133 / 169,
+    // drawn 125 / 169; with 54 000 one lane takes 0.99 to 1.05 of the time of two,
+    // from 58 000 on 0.87 to 0.95. Two substeps without a costmap are faster on one
+    // lane at any of these sizes (33 000 x 30 intervals: with selection 0.91 of the
+    // time, in chunks 0.97, drawn 0.90).
+    // And, with given controls and no selection, at every size: two waves of two
+    // lanes do beat one of one lane, whose cells such a kernel does not request
+    // ahead. 65 000 candidates, two lanes against one: 2 substeps x 30 intervals
+    // 62.1 and 64.9 us, 5 x 20 100.7 and 107.3, 20 x 8 158.9 and 173.6; with a
+    // costmap 4 x 20 85.5 and 95.3. Not so in the chunked form (4 x 24 111.6 and
+    // 100.4), with selection (123.0 and 114.6) and drawn (4 x 20 87 and 79).
+    if (lanes == 1 && a.K < 65536 && a.method == 0 && a.S > 1 &&
+        (kind == Kind::plain || ((a.S > 2 || a.has_costmap) &&
+                                 8 * (((long long)a.K + 63) / 64) < 7 * (long long)c->simds))) {
         lanes = 2;
         block = 64;
     }

@@ -69,3 +69,52 @@ def test_gradient(K, S, lanes):
         Jh, gh = run()
         assert torch.equal(J, Jh) and torch.equal(gr, gh)
     pl.close()
+
+
+@pytest.mark.parametrize("costmap", [False, True])
+@pytest.mark.parametrize("K,S,lanes", [(32769, 1, 1), (32769, 2, None), (41313, 10, 2),
+                                       (57280, 3, 2), (57281, 3, 1), (65535, 3, 1)])
+def test_other_forms(K, S, lanes, costmap):
+    """Selection, chunks and drawn controls: two lanes below seven eighths of a
+    wave per SIMD of one lane each (57 344 candidates on 1 024 of them), except
+    two substeps without a costmap."""
+    lanes = lanes or (2 if costmap else 1)
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    N = 3
+    w = inputs.c2(K=8, N=8)
+    T = w.terrain
+    g = torch.Generator(device="cuda")
+    g.manual_seed(K + S)
+    pl = P.Planner(w.vehicle, w.cost, dict(w.integ, substeps=S), K, N, T.W, T.H)
+    cm = torch.rand(T.H, T.W, generator=g, device="cuda") if costmap else None
+    pl.set_terrain(torch.from_numpy(T.height).cuda(), T.x0, T.y0, T.res, cm)
+    pl.set_order(P.PLAN_ORDER_OFF)
+    u = 0.3 * torch.randn(N, 2, K, generator=g, device="cuda")
+    spec = P.sample_spec(P.PLAN_SAMPLE_GAUSSIAN, 5, 6, (0.3, 0.3), None, False, N)
+
+    def run(expect=None):
+        out = []
+        J = torch.full((K,), -7.0, device="cuda")
+        plan = torch.full((N, 2), -7.0, device="cuda")
+        best = pl.rollout_argmin(w.state0, u, J, plan)
+        out += [J, plan, torch.tensor(best, dtype=torch.float64)]
+        assert expect is None or pl.get_launch()[0] == expect
+        J = torch.full((K,), -7.0, device="cuda")
+        pl.rollout_sampled(w.state0, spec, N, J)
+        out.append(J)
+        assert expect is None or pl.get_launch()[0] == expect
+        x, J = torch.empty(13, K, device="cuda"), torch.empty(K, device="cuda")
+        pl.init_state(w.state0, x, J)
+        pl.rollout_chunk(x, J, u, 0, 2, False)
+        pl.rollout_chunk(x, J, u, 2, N, True)
+        assert expect is None or pl.get_launch()[0] == expect
+        return out + [x, J]
+
+    got = run(lanes)
+    assert torch.isfinite(got[0]).any()
+    for hand in (1, 2):
+        pl.set_launch(hand, 0)
+        for a, b in zip(got, run()):
+            assert torch.equal(a, b)
+    pl.close()

@@ -1038,7 +1038,12 @@ static plan_status_t grad_check(plan_ctx *c, const char *fn, const float *state0
 // round takes 4, 0.16 a step and 0.5 for each step that it recomputes in
 // series: per window of states the longest segment's, or the eight of two
 // passes of four. Over 275 sizes that picks the faster one, or one at most 5 %
-// slower. With the forward pass, parallel against serial: K = 16 to 1 024, N = 1
+// slower. A candidate at its goal takes no more steps, and a serial step that is
+// not taken lasts 0.3 us, so that where every candidate arrives early the second
+// and further rounds need 15 steps each: 4 096 x 32 with the goal 3, 10 and more
+// than 32 steps away 50.2 / 37.9, 55.3 / 49.6 and 74.0 / 94.5, x 60 60.3 / 62.7,
+// 75.8 / 85.9 and 113 / 166; 6 000 x 60 83.0 / 66.3, 104 / 89.4 and 151 / 170, x 90
+// 93.8 / 94.1, 117 / 129 and 203 / 254. With the forward pass, parallel against serial: K = 16 to 1 024, N = 1
 // 14.7 / 15.4, 5 18.9 / 22.4, 100 83 / 245; 4 096 x 5 44.6 / 22.0, x 20 63.9 /
 // 60.5, x 100 213 / 265; 6 000 x 20 85.8 / 65.8, x 40 (four substeps of ten)
 // 112.6 / 112.1, x 100 224 / 270; 4 096 x 2 of 160 substeps 1 044 / 772. At
@@ -1051,7 +1056,8 @@ static bool linear_wanted(const plan_ctx *c, int K, int N, int S) {
     if (ckpt * ckpt > 4.0 * 13.0 * 14.0 * (double)N * S) return false;
     const double steps = (double)N * S, rounds = (K - 1) / c->simds + 1;
     const double windows = ((N - 1) / longest + 1);
-    return rounds * (4.0 + 0.16 * steps + 0.5 * windows * (S > 8 ? S : 8)) <= 2.0 * steps;
+    return (rounds == 1.0 || steps >= 15.0 * rounds) &&
+           rounds * (4.0 + 0.16 * steps + 0.5 * windows * (S > 8 ? S : 8)) <= 2.0 * steps;
 }
 
 // Its checkpoint interval in the workspace that interval C sizes. It wants

@@ -70,3 +70,17 @@ def test_equals_the_serial_pass(N, S, reach):
         np.testing.assert_array_equal(J, Jw[:K])
         assert np.array_equal(G == 0, r == 0)
         assert (np.abs(G - r).max(axis=(0, 1)) <= tol * np.abs(r).max(axis=(0, 1))).all()
+
+
+# (rounds of one workgroup a compute unit, intervals, substeps)
+@pytest.mark.parametrize("rounds,N,S", [(2, 12, 1), (3, 24, 1), (4, 32, 1), (6, 60, 1),
+                                        (4, 10, 3), (6, 8, 10)])
+def test_short_horizons_of_many_take_the_serial_pass(rounds, N, S):
+    """Where the serial pass skips most of few steps, several rounds of the
+    parallel one lose: those launches have the serial pass's bits."""
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    sizes = [24 * units + 8, 4 * units * rounds]
+    (Jw, Gw), (J, G) = grads(N, S, 4 if S < 4 else 1, sizes)
+    assert Gw.any()
+    np.testing.assert_array_equal(J, Jw[:sizes[1]])
+    np.testing.assert_array_equal(G, Gw[:, :, :sizes[1]])

@@ -1099,11 +1099,14 @@ static plan_status_t grad_launch(plan_ctx *c, const float *state0, const float *
     // forward pass in one launch, storing the state at every C-th interval
     int lanes, block;
     auto_launch(K, c->simds, &lanes, &block);
-    // Several substeps keep two lanes below 65 536 candidates. 50 000 candidates,
-    // two lanes against one: 20 intervals of 4 441 and 455 us, 12 of 10 693 and 722,
-    // 15 of 30, whose segments no cache holds, 4 367 and 5 812; but 60 of 1 338 and
-    // 330, 30 of 2 333 and 331.
-    if (lanes == 1 && K < 65536 && a.S > 2) {
+    // Two lanes below 65 536 candidates: the backward pass takes most of the time,
+    // and once its states outgrow the caches two waves a SIMD hide more of the waits
+    // for them than one. Two lanes against one, candidates x intervals: 40 000 x 80
+    // 436 and 436 us, x 120 670 and 1 003, x 250 1 759 and 2 507; 62 000 x 120 821 and
+    // 1 134, x 60 of two substeps 926 and 1 063; 50 000 x 12 of ten 693 and 722, x 15
+    // of thirty 4 367 and 5 812. Shorter ones take 3 % longer at most (50 000 x 30 of
+    // two 338 and 330).
+    if (lanes == 1 && K < 65536) {
         lanes = 2;
         block = 64;
     }

@@ -43,8 +43,8 @@ def test_given_controls(K, S, lanes, costmap):
     pl.close()
 
 
-@pytest.mark.parametrize("K,S,lanes", [(32769, 1, 1), (32769, 2, 1), (32769, 3, 2), (65535, 8, 2),
-                                       (65536, 8, 1)])
+@pytest.mark.parametrize("K,S,lanes", [(32769, 1, 2), (32769, 2, 2), (32769, 3, 2), (65535, 1, 2),
+                                       (65535, 8, 2), (65536, 1, 1), (65536, 8, 1)])
 def test_gradient(K, S, lanes):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")

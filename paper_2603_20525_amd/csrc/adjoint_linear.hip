@@ -343,6 +343,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void adjoint_linear(
     const float *up = a.controls + kc;
     const Arm arms[1] = {arm(a, wheel_i)};
     const bool finite_c = isfinite(a.cost[kc]);
+    const bool some = __any(finite_c);  // of the workgroup's four
 
     // the pull-back: lane j of candidate cj
     const int j = lane & 15, cj = lane >> 4;
@@ -365,8 +366,9 @@ __global__ __launch_bounds__(64 * WAVES, 1) void adjoint_linear(
         return isfinite(a.cost[k]) && !(m < WILD_RATE);
     };
 
-    // The states at which candidate kc's steps of segments [lo, hi) start.
-    auto recompute = [&](size_t kc, int lo, int hi) {
+    // The states at which candidate kc's steps of segments [lo, hi) start; one with
+    // a cost that is not finite has gradient zero and takes none.
+    auto recompute = [&](size_t kc, bool finite, int lo, int hi) {
         const float *up = a.controls + kc;
         const int n_lo = lo * C;
         for (int seg = lo + (t >> 4); seg < hi; seg += 4 * WAVES) {
@@ -384,7 +386,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void adjoint_linear(
                 const size_t nn = (size_t)min(n + 1, n1 - 1);
                 for (int s = 0; s < S; ++s, ++idx) {
                     const float gdx = st[0] - a.goal_x, gdy = st[1] - a.goal_y;
-                    const bool live = !(fmaf(gdx, gdx, gdy * gdy) <= a.goal_r2);
+                    const bool live = finite && !(fmaf(gdx, gdx, gdy * gdy) <= a.goal_r2);
                     if (wheel_i == 0) {
                         float *sl = &L.st[idx][c][0];
 #pragma unroll
@@ -416,7 +418,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void adjoint_linear(
             lam = j == 0 ? lx : j == 1 ? ly : 0.0f;
         }
         // entries no step writes
-        for (int i = t; i < 2 * BATCH * 4 * 16; i += 64 * WAVES) {
+        for (int i = some ? t : 2 * BATCH * 4 * 16; i < 2 * BATCH * 4 * 16; i += 64 * WAVES) {
             Batch &B = L.batch[i / (BATCH * 4 * 16)];
             const int o = i % (BATCH * 4 * 16);
             float4 *cl = &B.col[0][0][0][0] + (o >> 4) * 48 + (o & 15);
@@ -432,19 +434,21 @@ __global__ __launch_bounds__(64 * WAVES, 1) void adjoint_linear(
             const int n_lo = lo * C;
             const int count = min(N, hi * C) - n_lo;  // their intervals
             __syncthreads();
-            recompute(kc, lo, hi);
+            if (some) recompute(kc, finite_c, lo, hi);
             __syncthreads();
-            // Steps after the four have reached the goal leave lam as it is: the
+            // Steps after the four have reached the goal leave lam as it is, and
+            // those of a candidate whose cost is not finite do not count: the
             // batches end before them, as the serial pass skips them. 6 000
             // candidates x 100 that reach it within 0, 10 and 30 steps: 163, 173 and
-            // 188 us with them, 63, 95 and 120 without, serially 86, 104 and 143; the
-            // test costs the others 1 % at most.
+            // 188 us with them, 63, 95 and 120 without, serially 86, 104 and 143; 516
+            // x 210 on ground that turns nearly all of them over 133 serially, 170 and
+            // 119. The test costs the others 1 % at most.
             const int steps = count * S;
             auto taken = [&](int i) {
                 return L.st[i][0][13] + L.st[i][1][13] + L.st[i][2][13] + L.st[i][3][13] != 0.0f;
             };
-            int cnt = steps;
-            if (!__any(taken(steps - 1))) {
+            int cnt = some ? steps : 0;
+            if (some && !__any(taken(steps - 1))) {
                 cnt = 0;
                 for (int i = 0; i < steps; i += 64)
                     cnt += __popcll(__ballot(i + lane < steps && taken(min(i + lane, steps - 1))));
@@ -547,7 +551,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void adjoint_linear(
             const int lo = max(hi - segs, 0);
             const int n_lo = lo * C;
             __syncthreads();
-            recompute(kr, lo, hi);
+            recompute(kr, true, lo, hi);
             __syncthreads();
             if (!redo) continue;
             float gdd = 0.0f, gax = 0.0f;

@@ -72,6 +72,41 @@ def test_equals_the_serial_pass(N, S, reach):
         assert (np.abs(G - r).max(axis=(0, 1)) <= tol * np.abs(r).max(axis=(0, 1))).all()
 
 
+
+@pytest.mark.parametrize("N,S", [(1, 1), (17, 1), (40, 1), (9, 17), (400, 1)])
+def test_candidates_without_a_finite_cost(N, S):
+    """Whole workgroups of them, some with one that has, and some without: zeros,
+    and the others' gradients as if they were not there."""
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    w = inputs.c2(K=8, N=8)
+    T = w.terrain
+    Kw = 24 * units + 8
+    pl = P.Planner(w.vehicle, w.cost, dict(w.integ, substeps=S, dt=0.01 * S), Kw, N, T.W, T.H)
+    pl.set_terrain(torch.from_numpy(T.height).cuda(), T.x0, T.y0, T.res)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N)
+    u = 0.05 * torch.randn(N, 2, Kw, generator=g, device="cuda")
+    bad = torch.zeros(Kw, dtype=torch.bool, device="cuda")
+    bad[:20] = True
+    bad[20:40:4] = True
+    bad[41:60] = True
+
+    def grad(u, K):
+        J, G = torch.full((K,), -7.0, device="cuda"), torch.full((N, 2, K), -7.0, device="cuda")
+        pl.rollout_grad(w.state0, u[:, :, :K].contiguous(), J, G, None, 10)
+        return J, G
+
+    ub = u.clone()
+    ub[N // 2, 1, bad] = float("nan")
+    for K in (19, 41, 4 * units - 1, Kw):
+        J, G = grad(u, K)
+        Jb, Gb = grad(ub, K)
+        b = bad[:K]
+        assert torch.isfinite(J).all() and G.any()
+        assert torch.isinf(Jb[b]).all() and not Gb[:, :, b].any()
+        assert torch.equal(Jb[~b], J[~b]) and torch.equal(Gb[:, :, ~b], G[:, :, ~b])
+    pl.close()
+
 # (rounds of one workgroup a compute unit, intervals, substeps)
 @pytest.mark.parametrize("rounds,N,S", [(2, 12, 1), (3, 24, 1), (4, 32, 1), (6, 60, 1),
                                         (4, 10, 3), (6, 8, 10)])

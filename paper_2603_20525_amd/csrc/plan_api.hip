@@ -512,9 +512,16 @@ static plan_status_t launch(plan_ctx *c, RolloutArgs &a, Kind kind) {
     // 62.1 and 64.9 us, 5 x 20 100.7 and 107.3, 20 x 8 158.9 and 173.6; with a
     // costmap 4 x 20 85.5 and 95.3. Not so in the chunked form (4 x 24 111.6 and
     // 100.4), with selection (123.0 and 114.6) and drawn (4 x 20 87 and 79).
-    if (lanes == 1 && a.K < 65536 && a.method == 0 && a.S > 1 &&
-        (kind == Kind::plain || ((a.S > 2 || a.has_costmap) &&
-                                 8 * (((long long)a.K + 63) / 64) < 7 * (long long)c->simds))) {
+    // One substep the same over long horizons with a costmap and given controls, in
+    // one launch, where every unit has three waves of one lane and some a fourth:
+    // 52 000 x 250 at 5 m/s 345 / 372 us, 56 000 x 250 357 / 390, x 150 177 / 182 (x 100
+    // 115 / 115, at 14 m/s 291 / 275); 49 000 x 250 313 / 282, 58 000 x 250 382 / 394.
+    const long long one = ((long long)a.K + 63) / 64;  // waves of one lane
+    const bool units_idle = 8 * one < 7 * (long long)c->simds;
+    if (lanes == 1 && a.K < 65536 && a.method == 0 &&
+        (a.S > 1 ? kind == Kind::plain || ((a.S > 2 || a.has_costmap) && units_idle)
+                 : (kind == Kind::plain || kind == Kind::fused) && a.has_costmap && a.N >= 128 &&
+                       units_idle && 4 * one > 3 * (long long)c->simds)) {
         lanes = 2;
         block = 64;
     }
@@ -572,6 +579,15 @@ static plan_status_t launch(plan_ctx *c, RolloutArgs &a, Kind kind) {
     if (!c->block_opt && lanes > 1 &&
         ((plan::steps_ahead(a, one_wave) && few) ||
          (plan::stages_ahead(a, one_wave) && (few || (lanes == 4 && !a.has_costmap)))))
+        block = 64;
+    // One lane and fewer waves than SIMDs: one-wave workgroups below seven eighths
+    // of them, where those of 256 threads leave compute units without one. From
+    // there on they are even, and the short rollouts with selection earn nothing
+    // back (above). 256 against 64 threads, 40 000 candidates: 250 steps 290 / 239 us,
+    // with a costmap 340 / 266, in chunks 319 / 257, with selection 300 / 250, x 60
+    // 65.6 / 71.5; Runge-Kutta x 100 with a costmap 414 / 378; 62 000 x 250 323 / 319.
+    if (!c->lanes_opt && !c->block_opt && lanes == 1 && !ordered &&
+        units_idle && !(fused && (long long)a.N * a.S < 100))
         block = 64;
     c->last_lanes = lanes;
     c->last_block = block;

@@ -62,7 +62,7 @@ def test_checkpoint_interval_changes_no_bit(lanes):
     pl.close()
 
 
-@pytest.mark.parametrize("K,lanes", [(16384, 4), (16385, 2), (32768, 2), (32769, 1), (70001, 1)])
+@pytest.mark.parametrize("K,lanes", [(16384, 4), (16385, 2), (32768, 2), (32769, 2), (65536, 1), (70001, 1)])
 def test_automatic_lanes_equal_the_smallest_launch(K, lanes):
     """Candidates of any launch of the serial pass have one gradient."""
     N, Km = 12, many()

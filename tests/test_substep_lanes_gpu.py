@@ -118,3 +118,46 @@ def test_other_forms(K, S, lanes, costmap):
         for a, b in zip(got, run()):
             assert torch.equal(a, b)
     pl.close()
+
+
+@pytest.mark.parametrize("K,N,costmap,plain,fused",
+                         [(32769, 99, False, (1, 64), (1, 256)), (32769, 100, True, (1, 64), (1, 64)),
+                          (49152, 128, True, (1, 64), (1, 64)), (49153, 127, True, (1, 64), (1, 64)),
+                          (49153, 128, True, (2, 64), (2, 64)), (49153, 128, False, (1, 64), (1, 64)),
+                          (57280, 128, True, (2, 64), (2, 64)), (57281, 128, True, (1, 256), (1, 256)),
+                          (65536, 3, False, (1, 256), (1, 256))])
+def test_one_substep(K, N, costmap, plain, fused):
+    """Lanes and threads of one substep an interval, in one launch, with selection
+    and in chunks (as without selection, but never two lanes), on 1 024 SIMDs."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    w = inputs.c2(K=8, N=8)
+    T = w.terrain
+    g = torch.Generator(device="cuda")
+    g.manual_seed(K + N)
+    pl = P.Planner(w.vehicle, w.cost, w.integ, K, N, T.W, T.H)
+    cm = torch.rand(T.H, T.W, generator=g, device="cuda") if costmap else None
+    pl.set_terrain(torch.from_numpy(T.height).cuda(), T.x0, T.y0, T.res, cm)
+    u = 0.3 * torch.randn(N, 2, K, generator=g, device="cuda")
+
+    def run(expect=None):
+        J, fs = torch.full((K,), -7.0, device="cuda"), torch.full((13, K), -7.0, device="cuda")
+        pl.rollout(w.state0, u, J, fs)
+        assert expect is None or pl.get_launch() == plain
+        Ja, plan = torch.full((K,), -7.0, device="cuda"), torch.full((N, 2), -7.0, device="cuda")
+        best = pl.rollout_argmin(w.state0, u, Ja, plan)
+        assert expect is None or pl.get_launch() == fused
+        x, Jc = torch.empty(13, K, device="cuda"), torch.empty(K, device="cuda")
+        pl.init_state(w.state0, x, Jc)
+        for n in range(0, N, 50):
+            pl.rollout_chunk(x, Jc, u, n, min(N, n + 50), n + 50 >= N)
+        assert expect is None or pl.get_launch() == (1, plain[1])
+        return J, fs, Ja, plan, torch.tensor(best, dtype=torch.float64), x, Jc
+
+    got = run(True)
+    assert torch.isfinite(got[0]).any()
+    for hand in ((1, 64), (1, 256), (2, 64)):
+        pl.set_launch(*hand)
+        for a, b in zip(got, run()):
+            assert torch.allclose(a, b, rtol=0.0, atol=0.0, equal_nan=True)
+    pl.close()

@@ -60,9 +60,9 @@ ALU_PEAK_GOPS = 256 * 4 * 16 * 2.4
 TRAFFIC_COUNTERS = {
     # fused kernel, one lane per candidate (c5, 256-thread workgroups) and four
     # lanes (c2, 64), no costmap, cell-coefficient terrain; copy calibration
-    # 262144 KiB read as 131084.48 KiB (x1.99981) and written as 262144.0 KiB (x1.0)
-    "c5": (60620.05, 273.69, 262144.0 / 131084.48, 1.0, "6cbe54554e71c441"),
-    "c2": (4978.78, 32.91, 262144.0 / 131084.48, 1.0, "6cbe54554e71c441"),
+    # 262144 KiB read as 131084.44 KiB (x1.99981) and written as 262144.0 KiB (x1.0)
+    "c5": (60620.14, 273.69, 262144.0 / 131084.44, 1.0, "4f6a3fe22f778b4b"),
+    "c2": (4979.88, 32.91, 262144.0 / 131084.44, 1.0, "4f6a3fe22f778b4b"),
 }
 ROLLOUT_SOURCES = ("rollout_step.h", "rollout_kernels.h", "rollout.hip",
                    "rollout_onelane_1wave.hip", "rollout_multilane.hip",

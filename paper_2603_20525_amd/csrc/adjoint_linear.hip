@@ -8,7 +8,7 @@
 // long as its instructions take one wave (2 us a step). Of these only the
 // product lam <- A^T lam depends on the step after it. So a workgroup of five
 // waves takes four candidates and, from the end of the horizon backwards,
-//   1. recomputes up to 192 steps' states from the checkpoints into LDS,
+//   1. recomputes up to 160 steps' states from the checkpoints into LDS,
 //      twenty segments at a time (sixteen lanes a segment: four candidates of
 //      four wheels);
 //   2. linearises sixteen steps at a time (four waves of four steps of four
@@ -19,10 +19,12 @@
 //      is a dozen multiply-adds whose other factor is broadcast along the row
 //      of sixteen lanes by DPP.
 //
-// 1 024 candidates x 100 steps: 29 us (six rounds of it at 6 000: 165) against
-// 204 us; of these 6 go to the start and the recomputation and the rest to
-// seven batches, bound by the linearisations' 700 vector instructions. A
-// chain step is 13 multiply-adds, five other vector instructions and four LDS
+// 1 024 candidates x 100 steps: 31 us (six rounds of it at 6 000: 167) against
+// 204 us; of these 6 go to the start and the recomputation and 3.5 to each of
+// seven batches. The linearisations' 700 vector instructions account for 1.4 of
+// those; the rest are waits, a third of the waves' cycles, for LDS (1 971 cycles
+// a wave of bank conflicts: candidates' columns are 768 bytes apart) and at the
+// barrier between two batches. A chain step is 13 multiply-adds, five other vector instructions and four LDS
 // reads, 160 cycles; read from LDS without the columns being fetched ahead and
 // with the broadcasts as moves it took 600 and bound the kernel (40 us).
 //

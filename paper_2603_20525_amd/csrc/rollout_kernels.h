@@ -142,7 +142,10 @@ __device__ __forceinline__ float simulate(const RolloutArgs &a, int k, int sub, 
         // call to call: 10 007 candidates x 73 steps 58.5 -> 45.5 us, with the
         // softmin, costmap and final states 66.7 -> 55.5 us; 16 000 x 90 with
         // a costmap 69.4 -> 55.6 us; 25 000 x 100 at two lanes 81.0 -> 72.9
-        // us; 4 096 x 100, whose cells stay in the L2, 58.0 -> 57.2 us.
+        // us; 4 096 x 100, whose cells stay in the L2, 1 to 2 % less (58.3 -> 57.1
+        // us). Inputs that the L2 still holds from the call before gain nothing
+        // from it beyond a wave per compute unit: 6 000 x 70 36.0 -> 38.5 us, with
+        // eight sets of controls in turn 38.6 -> 34.3.
         bool done = false;
         float kept[14];
 #pragma unroll

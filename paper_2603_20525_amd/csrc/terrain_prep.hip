@@ -23,11 +23,12 @@ namespace {
 // 512 000 results), and the zeros around the band add nothing to a finite
 // window, so the sums are the bits of the scalar loop
 //   acc = fmaf(w[k], x[k], acc), k = 0 .. 2r,
-// which a workgroup still runs where its windows
-// hold an infinity or a NaN, whose product with the band's zeros would
-// spread. 16 x 16 wastes 15 of 2r + 16 columns of the band (32 x 32 twice
-// that) and takes half the cycles of vector fused multiply-adds. Bound: the
-// matrix cores at large sigma, the grid's reads and writes at small.
+// except the sign of a zero that underflow leaves (of heights around 1e-41). A
+// workgroup still runs that loop where its windows hold an infinity or a NaN,
+// whose product with the band's zeros would spread. 16 x 16 wastes 15 of
+// 2r + 16 columns of the band (32 x 32 twice that) and takes half the cycles of
+// vector fused multiply-adds. Bound: the matrix cores at large sigma, the
+// grid's reads and writes at small.
 // Measured, both passes, before (register windows on the vector ALUs) and
 // now: 2048 x 2048 nodes at 19, 37 and 181 taps 27.1, 33.4 and 86.2 us ->
 // 17.3, 22.1 and 48.3 us; 1537 x 1025 at 181 taps 52.7 -> 33.2 us.

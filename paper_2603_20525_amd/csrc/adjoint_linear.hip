@@ -24,7 +24,8 @@
 // seven batches. The linearisations' 700 vector instructions account for 1.4 of
 // those; the rest are waits, a third of the waves' cycles, for LDS (1 971 cycles
 // a wave of bank conflicts: candidates' columns are 768 bytes apart) and at the
-// barrier between two batches. A chain step is 13 multiply-adds, five other vector instructions and four LDS
+// barrier between two batches. A chain step is 13 multiply-adds, five other
+// vector instructions and four LDS
 // reads, 160 cycles; read from LDS without the columns being fetched ahead and
 // with the broadcasts as moves it took 600 and bound the kernel (40 us).
 //
